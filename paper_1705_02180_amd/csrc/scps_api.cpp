@@ -664,12 +664,12 @@ scps_status make_pairmajor(scps_ctx *c, SysHost &h) {
         h.d_G = nullptr;
         h.K_pm = 0;
         HIP_TRY(c, dalloc(c, &h.d_stack_pm, (size_t)stack_pm_width(h.K) * h.ntile_c * 4096));
-        HIP_TRY(c, dalloc(c, &h.d_G, (size_t)h.K * h.K));
+        HIP_TRY(c, dalloc(c, &h.d_G, (size_t)h.K * h.K + stack_finish_scratch(h.K)));   // G, then its partial sums
         h.K_pm = h.K;
     }
-    HIP_TRY(c, hipMemsetAsync(h.d_G, 0, (size_t)h.K * h.K * sizeof(double), c->stream));
-    HIP_TRY(c, launch_stack_pairmajor(h.nc, h.ncb, h.K, h.d_stack, h.d_stack_pm, c->stream));
-    HIP_TRY(c, launch_stack_gram(h.nc, h.ncb, h.K, c->prm.min_seq_sep, h.d_perm, h.d_stack, h.d_G, c->stream));
+    HIP_TRY(c, hipMemsetAsync(h.d_G, 0, ((size_t)h.K * h.K + stack_finish_scratch(h.K)) * sizeof(double), c->stream));
+    HIP_TRY(c, launch_stack_finish(h.nc, h.ncb, h.K, c->prm.min_seq_sep, h.d_perm, h.d_stack, h.d_stack_pm,
+                                   h.d_G + (size_t)h.K * h.K, h.d_G, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->jref_init = true;
     return SCPS_OK;

@@ -175,11 +175,12 @@ hipError_t launch_scps_eff(const SysDesc *sysd, const RepDesc *reps, const ScpsG
 hipError_t launch_scps_bias(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
                             const ScpsItem *items, int n_items, int max_frames, const float4 *xs, const float *coef,
                             const double *csum, int kmax, double *acc, hipStream_t st);
-hipError_t launch_stack_pairmajor(int nc, int ncb, int K, const float *stack, float *stack_pm, hipStream_t st);
-// G[j][k] = sum over the counted contact pairs of (R_j - R_k)^2 in float64 from
-// a tile-major stack; G must be zero on entry.
-hipError_t launch_stack_gram(int nc, int ncb, int K, int min_sep, const int *perm, const float *stack, double *G,
-                             hipStream_t st);
+// The pair-major copy of a tile-major stack and G[j][k] = sum over the counted
+// contact pairs of (R_j - R_k)^2 in float64; part: stack_finish_scratch(K)
+// doubles of scratch, zero on entry.
+size_t stack_finish_scratch(int K);
+hipError_t launch_stack_finish(int nc, int ncb, int K, int min_sep, const int *perm, const float *stack,
+                               float *stack_pm, double *part, double *G, hipStream_t st);
 
 // Neighbour lists of the cutoff variant (rMD with both cutoffs): NL_CAP
 // entries per particle, radius (larger cutoff) + NL_SKIN.

@@ -383,116 +383,214 @@ hipError_t launch_tile_sumsq(int nc, int ncb, int min_sep, const int *perm, cons
     return hipGetLastError();
 }
 
-// Pair-major copy of a frame stack: stack_pm[tile][p][k] = stack[tile][k][p]
-// for k < K (zero for K <= k < K4).  Grid (tile, STACKPM_SPLIT): each
-// workgroup transposes 64 / STACKPM_SPLIT sub-steps of one tile, 64 pairs at
-// a time through LDS; thread (w, l) reads rows k = w, w + 4, ...
-#ifndef STACKPM_SPLIT
-#define STACKPM_SPLIT 1
-#endif
-__global__ __launch_bounds__(256) void k_stack_pairmajor(int K, const float *__restrict__ stack,
-                                                         float *__restrict__ stack_pm) {
-    __shared__ float buf[64][KMAX + 1];
-    const int tile = blockIdx.x;
-    const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+// What the SCPS passes need of a new frame stack, in one pass over it: the
+// pair-major copy stack_pm[tile][p][k] = stack[tile][k][p] (k < K; zero for
+// K <= k < K4), and the frame distances G[j][k] = sum over the counted contact
+// pairs (both in the contact set, beyond min_seq_sep, each unordered pair
+// once) of (R_jp - R_kp)^2, in float64 from the float32 frames (differences of
+// float32 values are exact in float64), the diagonal 0.  part
+// (stack_finish_scratch doubles) must be zero on entry.
+//
+// A work unit is `per` sub-steps of a tile; workgroups stride over the units.
+// 64 pairs (32 when K > 64) at a time are staged twice in LDS: as float32 rows
+// to be written out pair by pair, and as float64 rows, zero for a pair that
+// does not count (so it adds nothing without a branch); the next batch's
+// loads are in flight meanwhile.  Frame k = r + N a has residue r mod N and
+// digit a < SF_B; thread t holds the SF_B x SF_B frame pairs of the residues
+// (r1, r2), r1 <= r2, number t mod n_blocks in registers and takes the pairs
+// p = t / n_blocks mod n_slices: 12 values read from LDS feed 36
+// subtract-and-FMA pairs (one frame pair per thread and read was bound by LDS
+// reads), neighbouring threads read neighbouring residues, and the rows have
+// odd lengths, so neither reads nor staging stores meet on a bank (blocks of
+// neighbouring frames in rows of even length did, and took twice the time).
+// Small stacks take short units (a tile of 10 frames in one workgroup was a
+// chain of 64 load-and-wait rounds).
+// Bound by float64 VALU issue.  6000 particles, 51 frames: 3.7 ms, 1.6 ms with
+// the distances left out (the copy and the distances in a kernel each took 3.1 +
+// 7.9 ms); 585 contact particles, 10 frames: 29 us (79 + 940 us).
+constexpr int SF_B = 6;
+constexpr int SF_COPIES = 64;
+constexpr int SF_STAGE = 16;   // 64 pairs x 64 frames or 32 x 128 over 256 threads
+static_assert(64 * 64 <= 256 * SF_STAGE && 32 * KMAX <= 256 * SF_STAGE, "a batch fits the staging registers");
+size_t stack_finish_scratch(int K) { return (size_t)SF_COPIES * K * (K - 1) / 2; }
+struct StackFinishShape {
+    int pairs;          // pairs per batch
+    int N;              // residues
+    int kf, kd;         // row lengths of the float32 and the float64 rows (odd)
+    size_t bytes;
+};
+static StackFinishShape stack_finish_shape(int K) {
+    StackFinishShape L;
+    L.pairs = K <= 64 ? 64 : 32;
+    L.N = (K + SF_B - 1) / SF_B;
+    L.kf = K | 1;
+    L.kd = (L.N * SF_B) | 1;
+    L.bytes = std::max((size_t)L.pairs * (L.kd * sizeof(double) + L.kf * sizeof(float)),
+                       (size_t)K * (K - 1) / 2 * sizeof(double));   // also the sums' meeting place
+    return L;
+}
+static_assert(((KMAX + SF_B - 1) / SF_B) * ((KMAX + SF_B - 1) / SF_B + 1) / 2 <= 256, "a thread for every block");
+
+template <int PAIRS>
+__global__ __launch_bounds__(256, 3) void k_stack_finish(int nc, int ncb, int K, int min_sep, int n_units, int per,
+                                                         int N, int kf, int kd, const int *__restrict__ perm,
+                                                         const float *__restrict__ stack,
+                                                         float *__restrict__ stack_pm, double *__restrict__ part) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int pairs = PAIRS, kstep = 256 / PAIRS;
+    double *rd = reinterpret_cast<double *>(smem);                    // [pairs][kd]
+    float *rf = reinterpret_cast<float *>(rd + (size_t)pairs * kd);   // [pairs][kf]
+    const int tid = threadIdx.x;
     const int K4 = stack_pm_width(K);
-    const int per = 64 / STACKPM_SPLIT, s_beg = blockIdx.y * per;
-    const float *src = stack + (int64_t)tile * K * 4096 + l;
-    for (int s = s_beg; s < s_beg + per; ++s) {
-        __syncthreads();
-        for (int k = w; k < K; k += 4) buf[l][k] = src[(int64_t)k * 4096 + s * 64];
-        __syncthreads();
-        float *out = stack_pm + ((int64_t)tile * 4096 + s * 64) * K4;
-        for (int e = tid; e < 64 * K4; e += 256) {
-            const int pl = e / K4, k = e - pl * K4;
-            out[e] = k < K ? buf[pl][k] : 0.f;
+    const int n_blocks = N * (N + 1) / 2, n_slices = 256 / n_blocks;
+    const int slice = tid / n_blocks;
+    const bool on = slice < n_slices;
+    int r1, r2;
+    tile_decode(tid % n_blocks, N, r1, r2);
+    double acc[SF_B][SF_B];
+#pragma unroll
+    for (int a = 0; a < SF_B; ++a)
+#pragma unroll
+        for (int b = 0; b < SF_B; ++b) acc[a][b] = 0.0;
+    for (int e = tid; e < pairs * kd; e += 256) rd[e] = 0.0;   // the columns past K stay zero
+    // thread tid stages pair p0 + tid mod pairs of frames tid / pairs, + 256 / pairs, ...:
+    // SF_STAGE values at most, loaded a batch ahead into registers
+    const int pl = tid & (pairs - 1), kt = tid / pairs;
+    const int upt = 64 / per, bpu = per * 64 / pairs;   // units of a tile, batches of a unit
+    float ahead[SF_STAGE];
+    bool cnt_ahead = false;
+    auto load = [&](int u, int q) {
+        const int tile = u / upt, p = (u - tile * upt) * per * 64 + q * pairs + pl, l = p & 63, sub = p >> 6;
+        int I, J;
+        tile_decode(tile, ncb, I, J);
+        const int a = I * 64 + l, b = J * 64 + ((l + sub) & 63);
+        cnt_ahead = a < nc && b < nc && tile_pair_counts(I == J, sub, l) && abs(perm[a] - perm[b]) > min_sep;
+        // (frames past K re-read frame 0: loads without branches)
+        const float *src = stack + (int64_t)tile * K * 4096;
+#pragma unroll
+        for (int s = 0; s < SF_STAGE; ++s) {
+            const int k = kt + s * kstep;
+            ahead[s] = src[(uint32_t)((k < K ? k : 0) * 4096 + p)];
         }
+    };
+    // the pair-major rows go out four frames at a time
+    const int w4 = K4 >> 2, dp = 256 / w4, dk = 256 - dp * w4;
+    int u = blockIdx.x, q = 0;
+    if (u < n_units) load(u, 0);
+    while (u < n_units) {
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < SF_STAGE; ++s) {
+            const int k = kt + s * kstep;
+            if (k < K) {
+                rf[pl * kf + k] = ahead[s];
+                rd[pl * kd + k] = cnt_ahead ? (double)ahead[s] : 0.0;
+            }
+        }
+        __syncthreads();
+        const int tile = u / upt, p0 = (u - tile * upt) * per * 64 + q * pairs;
+        if (++q == bpu) {
+            q = 0;
+            u += gridDim.x;
+        }
+        if (u < n_units) load(u, q);
+        {
+            float4 *out = reinterpret_cast<float4 *>(stack_pm + ((int64_t)tile * 4096 + p0) * K4);
+            int po = tid / w4, ko = tid - po * w4;
+            while (po < pairs) {
+                const float *row = rf + po * kf + 4 * ko;
+                const int left = K - 4 * ko;
+                out[po * w4 + ko] = make_float4(row[0], left > 1 ? row[1] : 0.f, left > 2 ? row[2] : 0.f,
+                                                left > 3 ? row[3] : 0.f);
+                po += dp;
+                ko += dk;
+                if (ko >= w4) {
+                    ko -= w4;
+                    ++po;
+                }
+            }
+        }
+        if (on)
+#pragma unroll 1
+            for (int p = slice; p < pairs; p += n_slices) {
+                const double *row1 = rd + p * kd + r1, *row2 = rd + p * kd + r2;
+                double rj[SF_B], rk[SF_B];
+#pragma unroll
+                for (int a = 0; a < SF_B; ++a) {
+                    rj[a] = *row1;
+                    rk[a] = *row2;
+                    row1 += N;
+                    row2 += N;
+                }
+#pragma unroll
+                for (int a = 0; a < SF_B; ++a)
+#pragma unroll
+                    for (int b = 0; b < SF_B; ++b) {
+                        const double d = rj[a] - rk[b];
+                        acc[a][b] = fma(d, d, acc[a][b]);
+                    }
+            }
     }
+    // The slices' sums meet in LDS (packed upper triangle; a residue with itself
+    // holds every pair twice, of which one counts), then go to one of SF_COPIES
+    // sets of partial sums: atomics on one address wait for each other (about
+    // 0.4 us each when workgroups of every XCD meet there).
+    const int E = K * (K - 1) / 2;
+    auto packed = [&](int j, int k) { return j * K - j * (j + 1) / 2 + k - j - 1; };
+    __syncthreads();
+    for (int e = tid; e < E; e += 256) rd[e] = 0.0;
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int a = 0; a < SF_B; ++a)
+#pragma unroll
+            for (int b = 0; b < SF_B; ++b) {
+                const int f1 = r1 + a * N, f2 = r2 + b * N, j = min(f1, f2), k = max(f1, f2);
+                if (f1 == f2 || k >= K || (r1 == r2 && a > b)) continue;
+                unsafeAtomicAdd(&rd[packed(j, k)], acc[a][b]);
+            }
+    }
+    __syncthreads();
+    double *Gp = part + (int64_t)(blockIdx.x % SF_COPIES) * E;
+    for (int e = tid; e < E; e += 256) unsafeAtomicAdd(&Gp[e], rd[e]);
 }
 
-hipError_t launch_stack_pairmajor(int nc, int ncb, int K, const float *stack, float *stack_pm, hipStream_t st) {
-    (void)nc;
+// G[j][k] = G[k][j] = the sum of the partial sets, in order; the diagonal 0
+__global__ void k_gram_sum(int K, const double *__restrict__ part, double *__restrict__ G) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, j = e / K, k = e - j * K, E = K * (K - 1) / 2;
+    if (j >= K || j > k) return;
+    double t = 0.0;
+    if (j < k) {
+        const double *p = part + (j * K - j * (j + 1) / 2 + k - j - 1);
+#pragma unroll 8
+        for (int c = 0; c < SF_COPIES; ++c) t += p[(int64_t)c * E];
+    }
+    G[j * K + k] = t;
+    G[k * K + j] = t;
+}
+
+hipError_t launch_stack_finish(int nc, int ncb, int K, int min_sep, const int *perm, const float *stack,
+                               float *stack_pm, double *part, double *G, hipStream_t st) {
     const int nt = ncb * (ncb + 1) / 2;
     if (nt == 0 || K == 0) return hipSuccess;
     if (K > KMAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_stack_pairmajor, dim3(nt, STACKPM_SPLIT), dim3(256), 0, st, K, stack, stack_pm);
-    return hipGetLastError();
-}
-
-// The stack's frame distances G[j][k] = sum over the counted contact pairs
-// (both in the contact set, beyond min_seq_sep, each unordered pair once) of
-// (R_jp - R_kp)^2, in float64 from the float32 frames (differences of float32
-// values are exact in float64), for j != k; the diagonal stays 0.  Grid
-// (tile, chunk): the workgroup stages the K frames of 64 pairs at a time in
-// LDS and each thread adds GRAM_EPT frame pairs j < k, numbered row by row,
-// over them; one float64 atomic per frame pair and workgroup at the end
-// (both G[j][k] and G[k][j]).  G must be zero on entry.
-constexpr int GRAM_EPT = 8;
-__global__ __launch_bounds__(256) void k_stack_gram(int nc, int ncb, int K, int min_sep,
-                                                    const int *__restrict__ perm, const float *__restrict__ stack,
-                                                    double *__restrict__ G) {
-    __shared__ float buf[64][KMAX + 1];
-    __shared__ int cnt[64];
-    __shared__ int orig[2][64];
-    const int tile = blockIdx.x;
-    int I, J;
-    tile_decode(tile, ncb, I, J);
-    const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
-    if (tid < 128) {
-        const int c = ((tid >> 6) ? J : I) * 64 + l;
-        orig[tid >> 6][l] = c < nc ? perm[c] : 0;
-    }
-    const int E = K * (K - 1) / 2;
-    int fj[GRAM_EPT], fk[GRAM_EPT];
-    double acc[GRAM_EPT];
-#pragma unroll
-    for (int m = 0; m < GRAM_EPT; ++m) {
-        int e = (blockIdx.y * GRAM_EPT + m) * 256 + tid;
-        int j = 0, k = 0;   // an entry past the end reads frame 0 twice and adds 0
-        if (e < E) {
-            while (e >= K - 1 - j) {
-                e -= K - 1 - j;
-                ++j;
-            }
-            k = j + 1 + e;
-        }
-        fj[m] = j;
-        fk[m] = k;
-        acc[m] = 0.0;
-    }
-    const float *src = stack + (int64_t)tile * K * 4096 + l;
-    for (int s = 0; s < 64; ++s) {
-        __syncthreads();
-        for (int k = w; k < K; k += 4) buf[l][k] = src[(int64_t)k * 4096 + s * 64];
-        if (w == 0) {
-            const int a = I * 64 + l, jl = (l + s) & 63, b = J * 64 + jl;
-            cnt[l] = a < nc && b < nc && tile_pair_counts(I == J, s, l) && abs(orig[0][l] - orig[1][jl]) > min_sep;
-        }
-        __syncthreads();
-        for (int p = 0; p < 64; ++p) {
-            if (!cnt[p]) continue;   // uniform across the workgroup
-#pragma unroll
-            for (int m = 0; m < GRAM_EPT; ++m) {
-                const double d = (double)buf[p][fj[m]] - (double)buf[p][fk[m]];
-                acc[m] = fma(d, d, acc[m]);
-            }
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < GRAM_EPT; ++m)
-        if (fj[m] != fk[m]) {
-            unsafeAtomicAdd(&G[fj[m] * K + fk[m]], acc[m]);
-            unsafeAtomicAdd(&G[fk[m] * K + fj[m]], acc[m]);
-        }
-}
-
-hipError_t launch_stack_gram(int nc, int ncb, int K, int min_sep, const int *perm, const float *stack, double *G,
-                             hipStream_t st) {
-    const int nt = ncb * (ncb + 1) / 2;
-    if (nt == 0 || K < 2) return hipSuccess;
-    if (K > KMAX) return hipErrorInvalidValue;
-    const int E = K * (K - 1) / 2, chunks = (E + GRAM_EPT * 256 - 1) / (GRAM_EPT * 256);
-    hipLaunchKernelGGL(k_stack_gram, dim3(nt, chunks), dim3(256), 0, st, nc, ncb, K, min_sep, perm, stack, G);
+    const StackFinishShape L = stack_finish_shape(K);
+    // the workgroups that are resident at once (256 CUs), each taking at least 8
+    // units where there are tiles enough, of one sub-step (64 pairs) at least; no
+    // more workgroups than leave each 4 units (their sums are K^2/2 atomics each)
+    const int resident = 256 * (int)std::min<size_t>(4, 160 * 1024 / L.bytes);
+    int per = 64;
+    while (per > 1 && (int64_t)nt * (64 / per) < 8 * resident) per /= 2;
+    const int64_t n_units = (int64_t)nt * (64 / per);
+    if (n_units > INT32_MAX) return hipErrorInvalidValue;
+    const int grid = (int)std::min<int64_t>((n_units + 3) / 4, resident);
+    if (L.pairs == 64)
+        hipLaunchKernelGGL(k_stack_finish<64>, dim3(grid), dim3(256), L.bytes, st, nc, ncb, K, min_sep, (int)n_units,
+                           per, L.N, L.kf, L.kd, perm, stack, stack_pm, part);
+    else
+        hipLaunchKernelGGL(k_stack_finish<32>, dim3(grid), dim3(256), L.bytes, st, nc, ncb, K, min_sep, (int)n_units,
+                           per, L.N, L.kf, L.kd, perm, stack, stack_pm, part);
+    hipLaunchKernelGGL(k_gram_sum, dim3((K * K + 63) / 64), dim3(64), 0, st, K, part, G);
     return hipGetLastError();
 }
 
