@@ -378,7 +378,9 @@ scps_status scps_autotune(scps_ctx *ctx, const float *x, const float *v, const d
 /* Fixes the launch configuration of scps_step_replicas for a context with
  * exec_mode AUTO, as scps_autotune would (e.g. one it chose earlier):
  *   path 0: the persistent kernel, param = threads per workgroup (64, 256,
- *           512, 1024; the replica's state must fit one workgroup's LDS);
+ *           512, 1024; the replica's state must fit one workgroup's LDS).  With
+ *           1024, a batch of at most 128 replicas, which leaves CUs idle, may
+ *           give each replica several workgroups, one launch per step;
  *   path 1: the per-step path (param ignored; the only path of an SCPS
  *           context);
  *   path 2: the packed persistent kernel, param = wavefronts per workgroup
@@ -387,7 +389,7 @@ scps_status scps_autotune(scps_ctx *ctx, const float *x, const float *v, const d
  * from 2048 replicas up) run packed with four wavefronts per workgroup and
  * longer ones on the persistent kernel where they fit (256 threads per
  * replica when a chain of at most 128 particles runs fewer than 512
- * replicas), else per step.  Results differ between configurations
+ * replicas, 1024 from 129 particles when at most 256 run), else per step.  Results differ between configurations
  * only by the order of float32 and float64 additions.  Host only.
  * Errors: INVALID_ARG (unknown path or parameter; paths 0 and 2 of an SCPS
  * context), SHAPE (the chains do not fit the configuration), STATE

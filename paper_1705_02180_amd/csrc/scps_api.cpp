@@ -38,8 +38,11 @@ struct SysHost {
     std::vector<uint64_t> tile_mask;    // [nb * nb]: sub-steps that need the per-pair predicates
     std::vector<int2> sched;            // persistent-kernel tile list, costliest first
     std::vector<uint64_t> sched_mask;   // its sub-step masks
-    int2 *d_sched = nullptr;
-    uint64_t *d_sched_mask = nullptr;
+    std::vector<int2> sched_f;          // the same work in short segments
+    std::vector<uint64_t> sched_f_mask;
+    double sched_cost = 0.0;            // in tiles of nonbonded pairs
+    int2 *d_sched = nullptr, *d_sched_f = nullptr;
+    uint64_t *d_sched_mask = nullptr, *d_sched_f_mask = nullptr;
     std::vector<float> mass, charge;
     int *d_perm = nullptr, *d_bond_next = nullptr;
     float *d_mass = nullptr, *d_charge = nullptr;
@@ -119,6 +122,8 @@ struct scps_ctx {
     int n_sitems = 0;
     int kmax = KMAX;
     int wg = 64;     // persistent workgroup size
+    int split_G = 1;          // workgroups per replica of the 1024-thread launch (> 1: one launch per step)
+    SplitBuffers split{};
     int tuned = -1;  // -1 untuned; else 0 persistent (with wg), 1 per-step, 2 packed (with pk_waves),
                      // from scps_autotune or scps_set_launch
     int pk_waves = 4;  // packed kernel: wavefronts per workgroup
@@ -232,7 +237,10 @@ scps_status upload_sysdesc(scps_ctx *c) {
         o.R2tile = h.d_R2tile;
         o.tiles = h.d_sched;
         o.tmask = h.d_sched_mask;
+        o.tiles_f = h.d_sched_f;
+        o.tmask_f = h.d_sched_f_mask;
         o.ntile = (int)h.sched.size();
+        o.ntile_f = (int)h.sched_f.size();
         o.Z0 = h.Z0;
     }
     HIP_TRY(c, hipMemcpy(c->d_sysd, d.data(), d.size() * sizeof(SysDesc), hipMemcpyHostToDevice));
@@ -254,11 +262,35 @@ bool usable(scps_ctx *c, scps_status *st) {
 int pick_wg(int nb, int n_replicas) {
     const int ntile = nb * (nb + 1) / 2;
     if (ntile >= 16) return 1024;
+    // three to five blocks: a replica a CU leaves room for 16 wavefronts (17 us
+    // a step against 32 with 256 threads at 200 particles x 64)
+    if (ntile >= 6 && n_replicas <= 256) return 1024;
     if (ntile >= 8) return 512;
     if (ntile >= 4) return 256;
     // a batch too small to give half the SIMDs (256 CUs x 4) a wavefront:
     // four wavefronts per replica share its tiles
     return n_replicas < 512 ? 256 : 64;
+}
+
+// Workgroups per replica of the 1024-thread launch: 1 (the persistent kernel,
+// one launch a call) or G > 1 (the split kernel, one launch a step), as many as
+// find a CU of their own and at least 4 short segments of the longest chain.
+// At G the pair phase of a replica takes 1.25 / G of its time on one CU (0.84 us
+// per tile of nonbonded pairs), and a launch and its update cost about 8 us more
+// than a step inside the persistent kernel, of which the persistent kernel's own
+// idle wavefronts take back 2 on small chains: measured 7.9 us persistent
+// against 11.2 split at 120 particles x 32, 18.8 against 13.1 at 200 x 64, 47.7
+// against 40 at 560 x 128 (G = 2).
+int pick_split(const scps_ctx *c) {
+    if (c->wg != 1024 || split_lds_bytes(c->n_pad_max) > 160 * 1024) return 1;
+    double cost = 0.0;
+    size_t items = 0;
+    for (int s : c->rep_sys) {
+        cost = std::max(cost, c->sys[s].sched_cost);
+        items = std::max(items, c->sys[s].sched_f.size());
+    }
+    const int G = std::min({256 / c->R, SPLIT_GMAX, (int)std::min<size_t>(items / 4, SPLIT_GMAX)});
+    return G > 1 && 0.84 * cost * (1.0 - 1.25 / G) > 6.0 ? G : 1;
 }
 
 // Per-tile flags and sub-step masks of a system (see TILE_* in scps_internal.h).
@@ -311,8 +343,10 @@ double tile_cost(int f, uint64_t mask) {
 // The persistent kernel's work list, costliest first; its wavefronts claim
 // entries dynamically in this order.  Off-diagonal tiles (I1, J), (I2, J) of
 // the same class (contact, mask) are paired; every tile or pair is cut into
-// segments of SEG_STEPS sub-steps (see SEG_STEPS for the encoding).
-void build_schedule(SysHost &h) {
+// segments of seg (seg2: double tile) sub-steps (see SEG_STEPS for the
+// encoding), the tail_items cheapest of them into shorter ones.
+void build_list(const SysHost &h, const int seg, const int seg2, const int tail_items, std::vector<int2> &codes,
+                std::vector<uint64_t> &masks, double *total) {
     struct Item {
         double cost;
         int2 code;
@@ -327,8 +361,10 @@ void build_schedule(SysHost &h) {
         uint64_t m = h.tile_mask[(size_t)I1 * h.nb + J];
         if (I2 >= 0) m |= h.tile_mask[(size_t)I2 * h.nb + J];
         if (m) f |= TILE_MASK;
-        for (int k = kb; k < ke; k += SEG_STEPS) {
-            const int k2 = std::min(k + SEG_STEPS, ke);
+        if (total) *total += cost * (ke - kb) / 64.0;
+        const int len = I2 >= 0 ? seg2 : seg;
+        for (int k = kb; k < ke; k += len) {
+            const int k2 = std::min(k + len, ke);
             all.push_back({cost * (k2 - k) / 64.0, code(I1, I2, J, f, k, k2), m});
         }
     };
@@ -359,7 +395,7 @@ void build_schedule(SysHost &h) {
     auto by_cost = [](const Item &a, const Item &b) { return a.cost > b.cost; };
     std::stable_sort(all.begin(), all.end(), by_cost);
     // cut the cheapest items into TAIL_STEPS-long pieces
-    const size_t first_tail = all.size() > (size_t)TAIL_ITEMS ? all.size() - TAIL_ITEMS : 0;
+    const size_t first_tail = all.size() > (size_t)tail_items ? all.size() - tail_items : 0;
     std::vector<Item> tail;
     for (size_t t = first_tail; t < all.size(); ++t) {
         const Item &it = all[t];
@@ -374,12 +410,17 @@ void build_schedule(SysHost &h) {
     all.resize(first_tail);
     std::stable_sort(tail.begin(), tail.end(), by_cost);
     all.insert(all.end(), tail.begin(), tail.end());
-    h.sched.clear();
-    h.sched_mask.clear();
+    codes.clear();
+    masks.clear();
     for (const auto &t : all) {
-        h.sched.push_back(t.code);
-        h.sched_mask.push_back(t.mask);
+        codes.push_back(t.code);
+        masks.push_back(t.mask);
     }
+}
+
+void build_schedule(SysHost &h) {
+    build_list(h, SEG_STEPS, SEG_STEPS, TAIL_ITEMS, h.sched, h.sched_mask, &h.sched_cost);
+    build_list(h, FINE_STEPS, FINE_STEPS / 2, 0, h.sched_f, h.sched_f_mask, nullptr);
 }
 
 // Replicas of each system in groups of up to SCPS_GROUP, one item per
@@ -544,6 +585,11 @@ scps_status init_impl(const scps_params *params, const scps_topology *topo, int3
         HIP_TRY(c, dalloc(c, &h.d_sched_mask, h.sched_mask.size()));
         HIP_TRY(c, hipMemcpy(h.d_sched_mask, h.sched_mask.data(), h.sched_mask.size() * sizeof(uint64_t),
                              hipMemcpyHostToDevice));
+        HIP_TRY(c, dalloc(c, &h.d_sched_f, h.sched_f.size()));
+        HIP_TRY(c, hipMemcpy(h.d_sched_f, h.sched_f.data(), h.sched_f.size() * sizeof(int2), hipMemcpyHostToDevice));
+        HIP_TRY(c, dalloc(c, &h.d_sched_f_mask, h.sched_f_mask.size()));
+        HIP_TRY(c, hipMemcpy(h.d_sched_f_mask, h.sched_f_mask.data(), h.sched_f_mask.size() * sizeof(uint64_t),
+                             hipMemcpyHostToDevice));
     }
     HIP_TRY(c, dalloc(c, &c->d_sysd, c->sys.size()));
     scps_status st = upload_sysdesc(c);
@@ -625,6 +671,16 @@ scps_status init_impl(const scps_params *params, const scps_topology *topo, int3
         HIP_TRY(c, dalloc(c, &c->d_zpart_nl, fc[R]));
         HIP_TRY(c, dalloc(c, &c->d_zbase, R));
         HIP_TRY(c, hipMemset(c->d_zbase, 0, R * sizeof(double)));
+    }
+    if (p.bias_mode == SCPS_BIAS_RMD && p.exec_mode == SCPS_EXEC_AUTO) c->split_G = pick_split(c);
+    if (c->split_G > 1) {
+        for (int k = 0; k < 2; ++k) {
+            HIP_TRY(c, dalloc(c, &c->split.xs[k], c->sumNpad));
+            HIP_TRY(c, dalloc(c, &c->split.vs[k], c->sumNpad));
+            HIP_TRY(c, dalloc(c, &c->split.zp[k], (size_t)R * c->split_G));
+        }
+        for (int k = 0; k < 3; ++k) HIP_TRY(c, dalloc(c, &c->split.acc[k], 6 * c->sumNpad));
+        HIP_TRY(c, hipMemset(c->split.acc[0], 0, 6 * c->sumNpad * sizeof(double)));
     }
     HIP_TRY(c, dalloc(c, &c->d_flags, R));
     HIP_TRY(c, hipMemset(c->d_flags, 0, R * sizeof(int)));
@@ -935,6 +991,11 @@ scps_status step_impl(scps_ctx *c, float *x, float *v, double *cv, int64_t n_ste
     if (path == 2) {
         HIP_TRY(c, launch_packed_rmd(c->pk_waves, c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, c->n_max, x, v, cv,
                                      n_steps, step0, record_every, frames, frame_stride, c->d_flags, c->stream));
+        return SCPS_OK;
+    }
+    if (path == 0 && c->wg == 1024 && c->split_G > 1) {
+        HIP_TRY(c, launch_split_rmd(c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, c->split_G, c->n_pad_max, c->split, x, v,
+                                    cv, n_steps, step0, record_every, frames, frame_stride, c->d_flags, c->stream));
         return SCPS_OK;
     }
     if (path == 0) {

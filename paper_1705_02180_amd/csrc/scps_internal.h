@@ -53,8 +53,9 @@ struct SysDesc {
     const double *R2tile;    // [ntile_c] per native-map tile: sum over its counted contact pairs of R^2
     const int2 *tiles;       // persistent work list, costliest first (see build_schedule)
     const uint64_t *tmask;   // per work-list item: sub-steps that need the per-pair predicates
-    int ntile;
-    int pad1;
+    const int2 *tiles_f;     // the same work in short segments, for many wavefronts per replica
+    const uint64_t *tmask_f;
+    int ntile, ntile_f;
     double Z0;
 };
 
@@ -116,6 +117,13 @@ constexpr int SEG_STEPS = SCPS_SEG_STEPS;
 constexpr int TAIL_ITEMS = SCPS_TAIL_ITEMS;
 constexpr int TAIL_STEPS = SCPS_TAIL_STEPS;
 
+// The short-segment list: segments of FINE_STEPS sub-steps of a tile (half as
+// many of a double tile, the same number of pairs).  The split kernel takes it
+// where the long-segment list has fewer than FINE_BELOW items for each of a
+// replica's wavefronts (the persistent kernel was no faster with it at 120 to
+// 300 particles).
+constexpr int FINE_STEPS = 16, FINE_BELOW = 3;
+
 // Frames per pair in the pair-major stack: K rounded up to a multiple of 4
 // (zero-filled), so a lane reads four frames of a pair with one 16-byte load.
 __host__ __device__ inline int stack_pm_width(int K) { return (K + 3) & ~3; }
@@ -133,6 +141,18 @@ hipError_t launch_persistent_rmd(int wg, int nbk, const KParams &P, const SysDes
                                  const int *order, int R, int n_pad_max, float *x, float *v,
                                  double *cv, int64_t n_steps, uint64_t step0, int record_every,
                                  float *frames, int64_t frame_stride, int *flags, hipStream_t st);
+// G workgroups of 1024 threads per replica, one launch per step.  xs, vs [sum
+// n_pad], acc [6 sum n_pad], zp [R][G]; acc[0] is zero on entry and on return.
+struct SplitBuffers {
+    float4 *xs[2], *vs[2];
+    double *acc[3], *zp[2];
+};
+constexpr int SPLIT_GMAX = 64;   // one lane per workgroup sums the z partials
+size_t split_lds_bytes(int n_pad);
+hipError_t launch_split_rmd(int nbk, const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R, int G,
+                            int n_pad_max, const SplitBuffers &B, float *x, float *v, double *cv, int64_t n_steps,
+                            uint64_t step0, int record_every, float *frames, int64_t frame_stride, int *flags,
+                            hipStream_t st);
 // Chains of at most 64 particles, 64 / n_max per wavefront, `waves` wavefronts
 // per workgroup, all n_steps in one launch; the untuned default for chains that
 // pack at least two to a wavefront.

@@ -442,6 +442,34 @@ __device__ __forceinline__ void bond_force(const KParams &P, float4 pa, float4 p
     f[2] = s * dz;
 }
 
+// One Langevin step of a particle from force F, in float64 on float32 state:
+// positions p.xyz, velocities q.xyz (BAOAB only).
+__device__ __forceinline__ void langevin_update(const KParams &P, const double inv_m, const double F[3],
+                                                const uint32_t atom, const uint32_t rep, const uint64_t step,
+                                                float4 &p, float4 &q) {
+    double g[3];
+    normals3(P, atom, rep, step, g[0], g[1], g[2]);
+    double X[3] = {(double)p.x, (double)p.y, (double)p.z};
+    if (P.integrator == 0) {
+        const double mob = P.dt * inv_m / P.gamma;
+        const double amp = sqrt(2.0 * P.kT * mob);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) X[c] += mob * F[c] + amp * g[c];
+    } else {
+        double V[3] = {(double)q.x, (double)q.y, (double)q.z};
+        const double amp = sqrt((1.0 - P.c1 * P.c1) * P.kT * inv_m);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            V[c] += P.dt * F[c] * inv_m;
+            X[c] += 0.5 * P.dt * V[c];
+            V[c] = P.c1 * V[c] + amp * g[c];
+            X[c] += 0.5 * P.dt * V[c];
+        }
+        q = make_float4((float)V[0], (float)V[1], (float)V[2], 0.f);
+    }
+    p = make_float4((float)X[0], (float)X[1], (float)X[2], p.w);
+}
+
 // ---------------------------------------------------------------------------
 // persistent rMD kernel: one workgroup runs one replica for all n_steps
 // ---------------------------------------------------------------------------
@@ -464,6 +492,86 @@ int persistent_max_npad(int wg) {
     return (n / 64) * 64;
 }
 
+
+// The pair phase of one replica whose positions (blocks twice), chain indices
+// and float64 accumulators [6][n_pad] lie in LDS: the work items first, first +
+// stride, ... of a list sorted costliest first.  Wavefront w starts with the
+// w-th of them and then claims the next one from *next (set to the number of
+// wavefronts).  Returns the lane's share of z.
+template <int NBK>
+__device__ __forceinline__ double pair_items(const KParams &P, const SysDesc &S, const int2 *__restrict__ tiles,
+                                             const uint64_t *__restrict__ tmask, const int ntile, const int first,
+                                             const int stride, const int lane, const int wave, const float4 *pos,
+                                             const int *org, double *acc, int *next) {
+    const int n = S.n, n_pad = S.n_pad;
+    double zacc = 0.0;
+    for (int q = wave; first + stride * q < ntile;) {
+        const int t = first + stride * q;
+        const int2 td = tiles[t];
+        const int I = td.x >> 16, J = td.x & 0xFFFF, tf = td.y & 0xFF, I2 = ((td.y >> 8) & 0xFF) - 1;
+        const int kb = (td.y >> 16) & 0x7F, ke = (td.y >> 23) & 0x7F;
+        const uint64_t mk = tmask[t];
+        if (I2 >= 0) {
+            // two off-diagonal tiles (I, J) and (I2, J) of the same class
+            LaneI A, B;
+            A.p = pos[I * 128 + lane];
+            B.p = pos[I2 * 128 + lane];
+            A.qp = P.dh_pref * A.p.w;
+            B.qp = P.dh_pref * B.p.w;
+            A.o = org[I * 64 + lane];
+            B.o = org[I2 * 64 + lane];
+            A.valid = I * 64 + lane < n;
+            B.valid = I2 * 64 + lane < n;
+            A.contact = I * 64 + lane < S.nc;
+            B.contact = I2 * 64 + lane < S.nc;
+            float fa[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            float fb[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            float fj[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            float zt = 0.f;
+            const bool con = tf & TF_CONTACT;
+            const float *rtA = con ? S.ref + (int64_t)tile_index(I, J, S.ncb) * 4096 : nullptr;
+            const float *rtB = con ? S.ref + (int64_t)tile_index(I2, J, S.ncb) * 4096 : nullptr;
+            int nxt = 0;
+            if (lane == 0) nxt = atomicAdd(next, 1);
+            tile_dispatch2<PM_RMD, NBK>(tf, kb, ke, mk, P, lane, A, B, pos + J * 128, org + J * 64, S.nc - J * 64,
+                                        rtA, rtB, fa, fb, fj, zt);
+            zacc += (double)zt;
+            const int ncomp = con ? 6 : 3;
+            const int jo = J * 64 + jflush_at(lane, ke);
+            for (int c = 0; c < ncomp; ++c) {
+                unsafeAtomicAdd(&acc[c * n_pad + I * 64 + lane], (double)fa[c]);
+                unsafeAtomicAdd(&acc[c * n_pad + I2 * 64 + lane], (double)fb[c]);
+                unsafeAtomicAdd(&acc[c * n_pad + jo], (double)fj[c]);
+            }
+            q = __builtin_amdgcn_readfirstlane(nxt);
+            continue;
+        }
+        LaneI A;
+        const int i = I * 64 + lane;
+        A.p = pos[I * 128 + lane];
+        A.qp = P.dh_pref * A.p.w;
+        A.o = org[i];
+        A.valid = i < n;
+        A.contact = i < S.nc;
+        float fi[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float fj[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float zt = 0.f;
+        const float *rt = (tf & TF_CONTACT) ? S.ref + (int64_t)tile_index(I, J, S.ncb) * 4096 : nullptr;
+        int nxt = 0;
+        if (lane == 0) nxt = atomicAdd(next, 1);
+        tile_dispatch<PM_RMD, NBK, SCPS_PAIR_GROUP>(tf, kb, ke, mk, P, lane, A, pos + J * 128, org + J * 64,
+                                                    S.nc - J * 64, rt, 0.f, fi, fj, zt);
+        zacc += (double)zt;
+        const int jo = J * 64 + jflush_at(lane, ke);
+        const int ncomp = (tf & TF_CONTACT) ? 6 : 3;
+        for (int c = 0; c < ncomp; ++c) {
+            unsafeAtomicAdd(&acc[c * n_pad + i], (double)fi[c]);
+            unsafeAtomicAdd(&acc[c * n_pad + jo], (double)fj[c]);
+        }
+        q = __builtin_amdgcn_readfirstlane(nxt);
+    }
+    return zacc;
+}
 
 // One workgroup per replica is resident per CU in the benchmark shapes, so
 // the register budget is WG/64/4 waves per SIMD: let the scheduler use it for
@@ -535,72 +643,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WG / 256 > 0
 
         // ---- pair phase: nonbonded + contact z and grad z, bonds ----------
         double zacc = 0.0;
-        // tiles are sorted costliest first; wavefront w starts with tile w and
-        // then takes the next unclaimed one
-        for (int t = wave; t < ntile;) {
-            const int2 td = S.tiles[t];
-            const int I = td.x >> 16, J = td.x & 0xFFFF, tf = td.y & 0xFF, I2 = ((td.y >> 8) & 0xFF) - 1;
-            const int kb = (td.y >> 16) & 0x7F, ke = (td.y >> 23) & 0x7F;
-            const uint64_t mk = S.tmask[t];
-            if (I2 >= 0) {
-                // two off-diagonal tiles (I, J) and (I2, J) of the same class
-                LaneI A, B;
-                A.p = pos[I * 128 + lane];
-                B.p = pos[I2 * 128 + lane];
-                A.qp = P.dh_pref * A.p.w;
-                B.qp = P.dh_pref * B.p.w;
-                A.o = org[I * 64 + lane];
-                B.o = org[I2 * 64 + lane];
-                A.valid = I * 64 + lane < n;
-                B.valid = I2 * 64 + lane < n;
-                A.contact = I * 64 + lane < S.nc;
-                B.contact = I2 * 64 + lane < S.nc;
-                float fa[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                float fb[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                float fj[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                float zt = 0.f;
-                const bool con = tf & TF_CONTACT;
-                const float *rtA = con ? S.ref + (int64_t)tile_index(I, J, S.ncb) * 4096 : nullptr;
-                const float *rtB = con ? S.ref + (int64_t)tile_index(I2, J, S.ncb) * 4096 : nullptr;
-                int nxt = 0;
-                if (lane == 0) nxt = atomicAdd(&sh_next, 1);
-                tile_dispatch2<PM_RMD, NBK>(tf, kb, ke, mk, P, lane, A, B, pos + J * 128, org + J * 64, S.nc - J * 64,
-                                            rtA, rtB, fa, fb, fj, zt);
-                zacc += (double)zt;
-                const int ncomp = con ? 6 : 3;
-                const int jo = J * 64 + jflush_at(lane, ke);
-                for (int c = 0; c < ncomp; ++c) {
-                    unsafeAtomicAdd(&acc[c * n_pad + I * 64 + lane], (double)fa[c]);
-                    unsafeAtomicAdd(&acc[c * n_pad + I2 * 64 + lane], (double)fb[c]);
-                    unsafeAtomicAdd(&acc[c * n_pad + jo], (double)fj[c]);
-                }
-                t = __builtin_amdgcn_readfirstlane(nxt);
-                continue;
-            }
-            LaneI A;
-            const int i = I * 64 + lane;
-            A.p = pos[I * 128 + lane];
-            A.qp = P.dh_pref * A.p.w;
-            A.o = org[i];
-            A.valid = i < n;
-            A.contact = i < S.nc;
-            float fi[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            float fj[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            float zt = 0.f;
-            const float *rt = (tf & TF_CONTACT) ? S.ref + (int64_t)tile_index(I, J, S.ncb) * 4096 : nullptr;
-            int nxt = 0;
-            if (lane == 0) nxt = atomicAdd(&sh_next, 1);
-            tile_dispatch<PM_RMD, NBK, SCPS_PAIR_GROUP>(tf, kb, ke, mk, P, lane, A, pos + J * 128, org + J * 64,
-                                                        S.nc - J * 64, rt, 0.f, fi, fj, zt);
-            zacc += (double)zt;
-            const int jo = J * 64 + jflush_at(lane, ke);
-            const int ncomp = (tf & TF_CONTACT) ? 6 : 3;
-            for (int c = 0; c < ncomp; ++c) {
-                unsafeAtomicAdd(&acc[c * n_pad + i], (double)fi[c]);
-                unsafeAtomicAdd(&acc[c * n_pad + jo], (double)fj[c]);
-            }
-            t = __builtin_amdgcn_readfirstlane(nxt);
-        }
+        zacc += pair_items<NBK>(P, S, S.tiles, S.tmask, ntile, 0, 1, lane, wave, pos, org, acc, &sh_next);
         for (int a = tid; a < n && P.has_bond; a += WG) {
             const int b = S.bond_next[a];
             if (b >= 0) {
@@ -740,6 +783,257 @@ hipError_t launch_persistent_rmd(int wg, int nbk, const KParams &P, const SysDes
         launch_persistent_wg<64>(nbk, P, sysd, reps, order, R, lds, x, v, cv, n_steps, step0, record_every,
                                  frames, frame_stride, flags, st);
         break;
+    }
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// split rMD step: G workgroups share a replica, one launch per step
+// ---------------------------------------------------------------------------
+// A batch with fewer replicas than CUs leaves the rest idle on the persistent
+// kernel (20 replicas of 560 particles: 46.6 us a step, as long as 256 take).
+// Here workgroup g of a replica takes every G-th work item.  A launch first
+// completes the previous step: every workgroup of the replica does the whole
+// update for itself (each needs most positions, and the idle CUs cost
+// nothing), from the forces, z partials and state the previous launch left in
+// global memory; workgroup 0 also writes state and cvstate.  Then it adds its
+// pairs' forces in LDS, and LDS into the replica's float64 accumulators.  So
+// one launch a step, with no wait inside a launch.  The state is double-
+// buffered (a launch reads one copy while workgroup 0 writes the other), the
+// accumulators are three: one read, one added to, one cleared for the next
+// launch; the last launch (update only) leaves the first one clear again.
+// Bound by the launch, the loads and the update (6 us, the update-only launch)
+// and a few us of pair phase and flush; the workgroups per replica share the
+// pair work at VALU issue.  us per step, persistent kernel -> split:
+//   n x replicas   560 x 2      560 x 20     560 x 64    560 x 128   971 x 12     1600 x 64    300 x 16
+//                  46.1 -> 12.2 47.2 -> 16.5 47.4 -> 25.9 47.7 -> 40 126.6 -> 23.3 440 -> 138  25.4 -> 12.2
+struct SplitStep {
+    const float4 *xa, *va;      // state before the update [sum n_pad], internal order
+    float4 *xb, *vb;            // after it
+    const double *acc_prev;     // forces at xa [sum 6 n_pad]
+    double *acc_cur, *acc_clear;
+    const double *zp_prev;      // [R][G] z partials at xa
+    double *zp_cur;
+    float *x, *v;               // the caller's state: read by the first launch, written by the last
+    double *cv;
+    float *frames;              // where this launch's state is recorded, or NULL
+    uint64_t step;              // of the update's noise
+    int G, first, last;
+    int *flags;
+};
+
+constexpr int SPLIT_PPT = 2;     // particles per thread
+size_t split_lds_bytes(int n_pad) {
+    if (n_pad > 1024 * SPLIT_PPT) return SIZE_MAX;
+    return (size_t)n_pad * (2 * sizeof(float4) + 6 * sizeof(double) + sizeof(int)) + 256;
+}
+
+template <int NBK>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_rmd_split(
+    const KParams P, const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps, const SplitStep A) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int WG = 1024, NW = WG / 64;
+    __shared__ double red_t[NW], red_z[NW];
+    __shared__ int sh_next;
+    const int g = blockIdx.x, r = blockIdx.y;
+    const RepDesc rd = reps[r];
+    const SysDesc S = sysd[rd.sys];
+    const int n = S.n, n_pad = S.n_pad;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float4 *pos = reinterpret_cast<float4 *>(smem);                   // [2 n_pad], blocks twice
+    double *acc = reinterpret_cast<double *>(pos + 2 * n_pad);        // [6][n_pad]
+    int *org = reinterpret_cast<int *>(acc + 6 * (size_t)n_pad);      // [n_pad]
+    const bool lead = g == 0;
+    double *c = A.cv + (int64_t)r * CV_STRIDE;
+
+    // ---- the previous step's update.  Everything it reads from global memory is
+    // requested first, so that one latency covers it all: the z partials, and
+    // state, forces and constants of this thread's particles
+    const bool has_v = A.v != nullptr, later = !A.first;
+    const float *xr = A.x + 3 * rd.off, *vr = has_v ? A.v + 3 * rd.off : nullptr;
+    const double zl = later && lane < A.G ? A.zp_prev[(int64_t)r * A.G + lane] : 0.0;
+    const double zm_in = __hip_atomic_load(&c[CV_ZM], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int po[SPLIT_PPT];
+    float4 pp[SPLIT_PPT], pq[SPLIT_PPT];
+    float pm[SPLIT_PPT];
+    double pf[SPLIT_PPT][6];
+#pragma unroll
+    for (int u = 0; u < SPLIT_PPT; ++u) {
+        const int a = tid + u * WG;
+        po[u] = a;
+        pp[u] = pad_position(a);
+        pq[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        pm[u] = 1.f;
+        if (a >= n) continue;
+        const int o = S.perm[a];
+        po[u] = o;
+        if (later) {
+            const double *ap = A.acc_prev + 6 * rd.poff + a;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) pf[u][k] = ap[k * n_pad];
+            pm[u] = S.mass[a];
+            pp[u] = A.xa[rd.poff + a];
+            if (has_v) pq[u] = A.va[rd.poff + a];
+        } else {
+            pp[u] = make_float4(xr[o], xr[n + o], xr[2 * n + o], S.charge[a]);
+            if (has_v) pq[u] = make_float4(vr[o], vr[n + o], vr[2 * n + o], 0.f);
+        }
+    }
+    if (!A.last) {
+        for (int e = tid; e < 6 * n_pad; e += WG) acc[e] = 0.0;
+        for (int e = g * WG + tid; e < 6 * n_pad; e += A.G * WG) A.acc_clear[6 * rd.poff + e] = 0.0;
+    }
+    // ratchet, eq (FrMD), at the positions of the forces: every wavefront takes
+    // the same fixed-order sum; the lead writes cvstate (a wavefront that reads the
+    // z_m it has already written computes the same min)
+    double scale = 0.0;
+    if (later) {
+        const double z = wave_sum(zl);
+        const double zm = fmin(zm_in, z);
+        const double dz = z - zm;
+        scale = -P.k_R * dz;
+        if (lead && tid == 0) {
+            c[CV_Z] = z;
+            __hip_atomic_store(&c[CV_ZM], zm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            c[CV_EB] = 0.5 * P.k_R * dz * dz;
+        }
+    }
+    double tsum = 0.0;
+    bool bad = false;
+#pragma unroll
+    for (int u = 0; u < SPLIT_PPT; ++u) {
+        const int a = tid + u * WG, o = po[u];
+        if (a >= n_pad) break;
+        float4 p = pp[u], q = pq[u];
+        if (a < n) {
+            if (later) {
+                const double inv_m = 1.0 / (double)pm[u];
+                double F[3], fb2 = 0.0;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const double fb = scale * pf[u][k + 3];
+                    F[k] = pf[u][k] + fb;
+                    fb2 = fma(fb, fb, fb2);
+                }
+                tsum = fma(fb2, inv_m, tsum);
+                langevin_update(P, inv_m, F, (uint32_t)o, P.rep_base + (uint32_t)r, A.step, p, q);
+                bad |= !(isfinite(p.x) && isfinite(p.y) && isfinite(p.z));
+            }
+            if (lead) {
+                if (A.frames) {
+                    float *fr = A.frames + 3 * rd.off;
+                    fr[o] = p.x;
+                    fr[n + o] = p.y;
+                    fr[2 * n + o] = p.z;
+                }
+                if (A.last) {
+                    float *xw = A.x + 3 * rd.off;
+                    xw[o] = p.x;
+                    xw[n + o] = p.y;
+                    xw[2 * n + o] = p.z;
+                    if (has_v) {
+                        float *vw = A.v + 3 * rd.off;
+                        vw[o] = q.x;
+                        vw[n + o] = q.y;
+                        vw[2 * n + o] = q.z;
+                    }
+                } else {
+                    A.xb[rd.poff + a] = p;
+                    if (has_v) A.vb[rd.poff + a] = q;
+                }
+            }
+        }
+        if (A.last) {
+            // the first launch of the next call adds to this buffer (it may be acc_prev,
+            // whose entries of particle a only this thread reads)
+            for (int k = 0; k < 6; ++k) A.acc_clear[6 * rd.poff + k * n_pad + a] = 0.0;
+        } else {
+            pos[dup_index(a)] = p;
+            pos[dup_index(a) + 64] = p;
+            org[a] = o;
+        }
+    }
+    if (lead) {
+        if (bad) A.flags[r] = 1;
+        tsum = wave_sum(tsum);
+        if (lane == 0) red_t[wave] = tsum;
+    }
+    if (tid == 0) sh_next = NW;
+    __syncthreads();
+    if (lead && tid == 0 && !A.first) {
+        double t = 0.0;
+        for (int w = 0; w < NW; ++w) t += red_t[w];
+        c[CV_T] += P.dt / P.gamma * t;
+    }
+    if (A.last) return;
+
+    // ---- pair phase: this workgroup's items, and its share of the bonds --------
+    const bool fine = S.ntile < FINE_BELOW * NW * A.G;
+    double zacc = pair_items<NBK>(P, S, fine ? S.tiles_f : S.tiles, fine ? S.tmask_f : S.tmask,
+                                  fine ? S.ntile_f : S.ntile, g, A.G, lane, wave, pos, org, acc, &sh_next);
+    for (int a = tid * A.G + g; a < n && P.has_bond; a += WG * A.G) {
+        const int b = S.bond_next[a];
+        if (b >= 0) {
+            double f[3];
+            bond_force(P, pos[dup_index(a)], pos[dup_index(b)], f);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                unsafeAtomicAdd(&acc[k * n_pad + a], f[k]);
+                unsafeAtomicAdd(&acc[k * n_pad + b], -f[k]);
+            }
+        }
+    }
+    zacc = wave_sum(zacc);
+    if (lane == 0) red_z[wave] = zacc;
+    __syncthreads();
+    double *ac = A.acc_cur + 6 * rd.poff;
+    for (int e = tid; e < 6 * n_pad; e += WG) {
+        const double f = acc[e];
+        if (f != 0.0) unsafeAtomicAdd(&ac[e], f);
+    }
+    if (tid == 0) {
+        double z = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) z += red_z[w];
+        A.zp_cur[(int64_t)r * A.G + g] = z;
+    }
+}
+
+hipError_t launch_split_rmd(int nbk, const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R, int G,
+                            int n_pad_max, const SplitBuffers &B, float *x, float *v, double *cv, int64_t n_steps,
+                            uint64_t step0, int record_every, float *frames, int64_t frame_stride, int *flags,
+                            hipStream_t st) {
+    const size_t lds = split_lds_bytes(n_pad_max);
+    for (int64_t m = 0; m <= n_steps; ++m) {
+        const int in = (int)(m & 1), out = in ^ 1, k = (int)(m % 3);
+        SplitStep A{};
+        A.first = m == 0;
+        A.last = m == n_steps;
+        A.xa = B.xs[in];
+        A.va = B.vs[in];
+        A.xb = B.xs[out];
+        A.vb = B.vs[out];
+        A.acc_prev = B.acc[(k + 2) % 3];
+        A.acc_cur = B.acc[k];
+        A.acc_clear = B.acc[A.last ? 0 : (k + 1) % 3];
+        A.zp_prev = B.zp[in];
+        A.zp_cur = B.zp[out];
+        A.x = x;
+        A.v = v;
+        A.cv = cv;
+        A.frames = record_every > 0 && m % record_every == 0 ? frames + (m / record_every) * frame_stride : nullptr;
+        A.step = step0 + (uint64_t)(m - 1);
+        A.G = G;
+        A.flags = flags;
+        const dim3 grid(A.last ? 1 : G, R);
+#define SCPS_LAUNCH(K) hipLaunchKernelGGL((k_rmd_split<K>), grid, dim3(1024), lds, st, P, sysd, reps, A)
+        switch (nbk) {
+        case 0: SCPS_LAUNCH(0); break;
+        case 1: SCPS_LAUNCH(1); break;
+        case 2: SCPS_LAUNCH(2); break;
+        default: SCPS_LAUNCH(3); break;
+        }
+#undef SCPS_LAUNCH
     }
     return hipGetLastError();
 }
@@ -1830,31 +2124,12 @@ __global__ __launch_bounds__(256) void k_integrate(const KParams P, const SysDes
             ar[(c + 3) * n_pad + a] = 0.0;
         }
         tb = fb2 * inv_m;
-        double g[3];
-        normals3(P, (uint32_t)S.perm[a], P.rep_base + (uint32_t)r, step, g[0], g[1], g[2]);
         float4 *xr2 = xs + 2 * rd.poff;
         const int da = dup_index(a);
-        const float4 p = xr2[da];
-        double X[3] = {(double)p.x, (double)p.y, (double)p.z};
-        if (P.integrator == 0) {
-            const double mob = P.dt * inv_m / P.gamma;
-            const double amp = sqrt(2.0 * P.kT * mob);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) X[c] += mob * F[c] + amp * g[c];
-        } else {
-            const float4 q = vs[rd.poff + a];
-            double V[3] = {(double)q.x, (double)q.y, (double)q.z};
-            const double amp = sqrt((1.0 - P.c1 * P.c1) * P.kT * inv_m);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                V[c] += P.dt * F[c] * inv_m;
-                X[c] += 0.5 * P.dt * V[c];
-                V[c] = P.c1 * V[c] + amp * g[c];
-                X[c] += 0.5 * P.dt * V[c];
-            }
-            vs[rd.poff + a] = make_float4((float)V[0], (float)V[1], (float)V[2], 0.f);
-        }
-        const float4 np = make_float4((float)X[0], (float)X[1], (float)X[2], p.w);
+        float4 np = xr2[da], q = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (P.integrator != 0) q = vs[rd.poff + a];
+        langevin_update(P, inv_m, F, (uint32_t)S.perm[a], P.rep_base + (uint32_t)r, step, np, q);
+        if (P.integrator != 0) vs[rd.poff + a] = q;
         if (!(isfinite(np.x) && isfinite(np.y) && isfinite(np.z))) flags[r] = 1;
         xr2[da] = np;
         xr2[da + 64] = np;
