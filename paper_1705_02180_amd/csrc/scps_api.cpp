@@ -120,6 +120,7 @@ struct scps_ctx {
     ScpsGroup *d_groups = nullptr;
     ScpsItem *d_sitems = nullptr;
     int n_sitems = 0;
+    int max_group = 0;            // replicas of the largest group
     int kmax = KMAX;
     int wg = 64;     // persistent workgroup size
     int split_G = 1;          // workgroups per replica of the 1024-thread launch (> 1: one launch per step)
@@ -449,6 +450,7 @@ scps_status ensure_scps_groups(scps_ctx *c) {
             ScpsGroup g{};
             g.sys = s;
             g.nrep = (int)std::min<size_t>(SCPS_GROUP, mine.size() - b);
+            c->max_group = std::max(c->max_group, g.nrep);
             for (int k = 0; k < g.nrep; ++k) g.rep[k] = mine[b + k];
             const int gi = (int)groups.size();
             groups.push_back(g);
@@ -919,7 +921,8 @@ scps_status step_launches(scps_ctx *c, double *cv, uint64_t step, const uint64_t
         // the nonbonded forces and bonds (mode 4, every tile pair) after it, or
         // joined from the side stream
         HIP_TRY(c, launch_scps_bias(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems,
-                                    max_stack_frames(c), c->d_xs, c->d_coef, c->d_csum, c->kmax, c->d_acc, st));
+                                    max_stack_frames(c), c->max_group, c->d_xs, c->d_coef, c->d_csum, c->kmax, c->d_acc,
+                                    st));
         if (tev) HIP_TRY(c, hipEventRecord(tev[3], st));
         if (overlap)
             HIP_TRY(c, hipStreamWaitEvent(st, c->ev_join, 0));

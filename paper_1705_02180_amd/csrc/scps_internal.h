@@ -192,9 +192,10 @@ hipError_t launch_scps_eff(const SysDesc *sysd, const RepDesc *reps, const ScpsG
                            int n_items, const float *coef, int kmax, float *E, hipStream_t st);
 // Effective references and the contact bias forces in one pass (no E in
 // device memory): adds the bias gradient terms to acc components 3..5.
+// max_group: the largest number of replicas in a group.
 hipError_t launch_scps_bias(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
-                            const ScpsItem *items, int n_items, int max_frames, const float4 *xs, const float *coef,
-                            const double *csum, int kmax, double *acc, hipStream_t st);
+                            const ScpsItem *items, int n_items, int max_frames, int max_group, const float4 *xs,
+                            const float *coef, const double *csum, int kmax, double *acc, hipStream_t st);
 // The pair-major copy of a tile-major stack and G[j][k] = sum over the counted
 // contact pairs of (R_j - R_k)^2 in float64; part: stack_finish_scratch(K)
 // doubles of scratch, zero on entry.

@@ -1050,63 +1050,125 @@ __device__ __forceinline__ void bias_loads(const float *tile_base, const int k, 
 // compile time so that a chain has no branches and its loads are issued
 // together.  With NH = 2 (stacks of more than 64 frames) the loads of the
 // next half are issued after the MFMAs of the current one.
-template <bool MASK, int KKN, int NH>
-__device__ __forceinline__ void scps_bias_tile(const KParams &P, const SysDesc &S, const ScpsItem &it,
-                                               const int lane, const int wave, const int kb, const int ke, BiasLds &L,
-                                               float fi[][3], float fj[][3]) {
+template <int KKN, int NH>
+__device__ __forceinline__ void scps_bias_produce(const SysDesc &S, const ScpsItem &it, const int lane,
+                                                  const int wave, const int kb, const int ke, BiasLds &L) {
+    const int nch = (ke - kb + BIAS_CH - 1) / BIAS_CH;
+    // ---- E of sub-step kb + BIAS_CH st + wave, chunk st -> buffer st & 1
+    const int K = S.K;
+    const int slot = lane & 31, half = lane >> 5;
+    const float *Rt = S.stack + (int64_t)it.tile * K * 4096;   // uniform
+    bias_f2 r[KKN];
+    if (kb + wave < ke) bias_loads<KKN>(Rt, kb + wave, 0, K, slot, half, r);
+#pragma unroll 1
+    for (int st = 0; st <= nch; ++st) {
+        const int k = kb + BIAS_CH * st + wave;
+        if (st < nch && k < ke) {
+            fvec16 acc[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+            // one chain per KKN frame pairs; a second chain's loads go out after
+            // the first chain's MFMAs, into the same registers
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+#pragma unroll
+                for (int kk = 0; kk < KKN; ++kk) {
+                    const float c = L.c[KKN * h + kk][lane];
+                    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[kk].x, c, acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[kk].y, c, acc[1], 0, 0, 0);
+                }
+                if (h + 1 < NH) bias_loads<KKN>(Rt, k, KKN * (h + 1), K, slot, half, r);
+            }
+            float(*E)[65] = L.E[st & 1][wave];
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) E[slot][16 * (v >> 2) + 8 * half + 2 * (v & 3) + b] = acc[b][v];
+            if (k + BIAS_CH < ke) bias_loads<KKN>(Rt, k + BIAS_CH, 0, K, slot, half, r);
+        }
+        __syncthreads();
+    }
+}
+
+// The same for a group of at most 16 replicas, with 16x16x4 float32 MFMAs
+// (half the matrix time): rows pairs 4 row + b of block b, read with one
+// 16-byte load per lane from frame 4 kk + (l >> 4); columns the slots l & 15.
+// Element v of lane l in block b is pair 16 (l >> 4) + 4 v + b.
+typedef float bias_f4 __attribute__((ext_vector_type(4)));
+template <int KKN>
+__device__ __forceinline__ void bias_loads16(const float *tile_base, const int k, const int f0, const int K,
+                                             const int lane, bias_f4 r[KKN]) {
+    typedef const __attribute__((address_space(1))) bias_f4 *gptr;
+    const gptr gb = (gptr)tile_base;
+    const int o = (lane >> 4) * 1024 + k * 16 + (lane & 15);   // in groups of four floats
+#pragma unroll
+    for (int kk = 0; kk < KKN; ++kk) {
+        r[kk] = bias_f4{0.f, 0.f, 0.f, 0.f};
+        if (4 * (f0 + kk) + (lane >> 4) < K) r[kk] = __builtin_nontemporal_load(gb + (o + (f0 + kk) * 4096));
+    }
+}
+
+template <int KKN, int NH>
+__device__ __forceinline__ void scps_bias_produce16(const SysDesc &S, const ScpsItem &it, const int lane,
+                                                    const int wave, const int kb, const int ke, BiasLds &L) {
+    const int nch = (ke - kb + BIAS_CH - 1) / BIAS_CH;
+    const int K = S.K;
+    const int slot = lane & 15, quad = lane >> 4;
+    const float *Rt = S.stack + (int64_t)it.tile * K * 4096;   // uniform
+    // c of frame 4 kk + quad: row 2 kk + quad / 2 of L.c, its lower or upper half
+    const float *cl = &L.c[quad >> 1][(quad & 1) * 32 + slot];
+    bias_f4 r[KKN];
+    if (kb + wave < ke) bias_loads16<KKN>(Rt, kb + wave, 0, K, lane, r);
+#pragma unroll 1
+    for (int st = 0; st <= nch; ++st) {
+        const int k = kb + BIAS_CH * st + wave;
+        if (st < nch && k < ke) {
+            bias_f4 acc[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[b] = bias_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+#pragma unroll
+                for (int kk = 0; kk < KKN; ++kk) {
+                    const float c = cl[128 * (KKN * h + kk)];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[kk][b], c, acc[b], 0, 0, 0);
+                }
+                if (h + 1 < NH) bias_loads16<KKN>(Rt, k, KKN * (h + 1), K, lane, r);
+            }
+            float(*E)[65] = L.E[st & 1][wave];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) E[slot][16 * quad + 4 * v + b] = acc[b][v];
+            if (k + BIAS_CH < ke) bias_loads16<KKN>(Rt, k + BIAS_CH, 0, K, lane, r);
+        }
+        __syncthreads();
+    }
+}
+
+// Pair wavefront pw: chunk st - 1 from buffer (st - 1) & 1, for its first SPW
+// slots (the wavefronts of a group of fewer than SCPS_GROUP replicas have fewer).
+template <bool MASK, int SPW>
+__device__ __forceinline__ void scps_bias_consume(const KParams &P, const SysDesc &S, const ScpsItem &it,
+                                                  const int lane, const int pw, const int kb, const int ke,
+                                                  BiasLds &L, float fi[][3], float fj[][3]) {
     const int I = it.IJ >> 16, J = it.IJ & 0xFFFF;
     const bool diag = it.flags & TILE_DIAG;
     const int nch = (ke - kb + BIAS_CH - 1) / BIAS_CH;
-    if (wave < BIAS_NMW) {
-        // ---- producer: E of sub-step kb + BIAS_CH st + wave, chunk st -> buffer st & 1
-        const int K = S.K;
-        const int slot = lane & 31, half = lane >> 5;
-        const float *Rt = S.stack + (int64_t)it.tile * K * 4096;   // uniform
-        bias_f2 r[KKN];
-        if (kb + wave < ke) bias_loads<KKN>(Rt, kb + wave, 0, K, slot, half, r);
-#pragma unroll 1
-        for (int st = 0; st <= nch; ++st) {
-            const int k = kb + BIAS_CH * st + wave;
-            if (st < nch && k < ke) {
-                fvec16 acc[2];
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
-                // one chain per KKN frame pairs; a second chain's loads go out after
-                // the first chain's MFMAs, into the same registers
-#pragma unroll
-                for (int h = 0; h < NH; ++h) {
-#pragma unroll
-                    for (int kk = 0; kk < KKN; ++kk) {
-                        const float c = L.c[KKN * h + kk][lane];
-                        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[kk].x, c, acc[0], 0, 0, 0);
-                        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[kk].y, c, acc[1], 0, 0, 0);
-                    }
-                    if (h + 1 < NH) bias_loads<KKN>(Rt, k, KKN * (h + 1), K, slot, half, r);
-                }
-                float(*E)[65] = L.E[st & 1][wave];
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) E[slot][16 * (v >> 2) + 8 * half + 2 * (v & 3) + b] = acc[b][v];
-                if (k + BIAS_CH < ke) bias_loads<KKN>(Rt, k + BIAS_CH, 0, K, slot, half, r);
-            }
-            __syncthreads();
-        }
-        return;
-    }
-    // ---- consumer: chunk st - 1 from buffer (st - 1) & 1
-    const int pw = wave - BIAS_NMW;
     const int nc = S.nc, min_sep = P.min_sep;
     const bool has_cut = P.has_cut;
     const float inv_r0sq = P.inv_r0sq, r_cut2 = P.r_cut2;
     const float cp0 = P.cp[0], cp1 = P.cp[1], cp2 = P.cp[2], cp3 = P.cp[3];
     const bool icon = I * 64 + lane < nc;
     const int oi = L.org[0][lane];
-    float px[BIAS_SPW], py[BIAS_SPW], pz[BIAS_SPW], csm[BIAS_SPW];
+    constexpr int SA = SPW > 0 ? SPW : 1;
+    float px[SA], py[SA], pz[SA], csm[SA];
 #pragma unroll
-    for (int m = 0; m < BIAS_SPW; ++m) {
+    for (int m = 0; m < SPW; ++m) {
         const float4 p = L.pos[0][pw + BIAS_NPW * m][lane];
         px[m] = p.x;
         py[m] = p.y;
@@ -1128,7 +1190,7 @@ __device__ __forceinline__ void scps_bias_tile(const KParams &P, const SysDesc &
                     bool conm = true;
                     if constexpr (MASK) conm = icon & (J * 64 + jl < nc) & (abs(oi - L.org[1][jl]) > min_sep);
 #pragma unroll
-                    for (int m = 0; m < BIAS_SPW; ++m) {
+                    for (int m = 0; m < SPW; ++m) {
                         const int sl = pw + BIAS_NPW * m;
                         const float4 pj = L.pos[1][sl][jl];
                         const float dx = px[m] - pj.x, dy = py[m] - pj.y, dz = pz[m] - pj.z;
@@ -1159,33 +1221,72 @@ __device__ __forceinline__ void scps_bias_tile(const KParams &P, const SysDesc &
     }
 }
 
-// BIG: stacks of 65 .. KMAX frames, in a kernel of its own so that the
-// common sizes keep their register allocation.
-template <bool MASK, bool BIG>
-__device__ __forceinline__ void scps_bias_dispatch(const KParams &P, const SysDesc &S, const ScpsItem &it,
-                                                   const int lane, const int wave, const int kb, const int ke,
-                                                   BiasLds &L, float fi[][3], float fj[][3]) {
-    if constexpr (BIG)
-        scps_bias_tile<MASK, 32, 2>(P, S, it, lane, wave, kb, ke, L, fi, fj);
-    else if (S.K <= 16)
-        scps_bias_tile<MASK, 8, 1>(P, S, it, lane, wave, kb, ke, L, fi, fj);
-    else if (S.K <= 32)
-        scps_bias_tile<MASK, 16, 1>(P, S, it, lane, wave, kb, ke, L, fi, fj);
-    else if (S.K <= 52)
-        scps_bias_tile<MASK, 26, 1>(P, S, it, lane, wave, kb, ke, L, fi, fj);
-    else
-        scps_bias_tile<MASK, 32, 1>(P, S, it, lane, wave, kb, ke, L, fi, fj);
+// BIG: stacks of 65 .. KMAX frames, HALF: no group of more than 16 replicas, in
+// kernels of their own so that each keeps its register allocation.  A sub-step's matrix work is
+// cut to the smallest of a few frame counts that holds the stack and to 16 or
+// 32 replicas, and a pair wavefront's to its replicas: 20 replicas x 1501
+// particles, 72 frames took 230 us a pass as 32 replicas with 128 frames,
+// 168 now; 8 x 2500 (1252 in contact), 33 frames 71 us as 32,
+// 33 now; 15 x 1700, 70 frames 241 -> 122 us.
+template <bool BIG, bool HALF>
+__device__ __forceinline__ void scps_bias_produce_any(const SysDesc &S, const ScpsItem &it, const int lane,
+                                                      const int wave, const int kb, const int ke, BiasLds &L) {
+    // KKN frame pairs, or half as many groups of four frames
+#define SCPS_PRODUCE(KKN, NH)                                                     \
+    do {                                                                           \
+        if constexpr (HALF)                                                        \
+            scps_bias_produce16<KKN / 2, NH>(S, it, lane, wave, kb, ke, L);        \
+        else                                                                       \
+            scps_bias_produce<KKN, NH>(S, it, lane, wave, kb, ke, L);              \
+    } while (0)
+    static_assert(KMAX / 2 == 64, "frame pairs of the largest stack");
+    if constexpr (BIG) {
+        if (S.K <= 72)
+            SCPS_PRODUCE(18, 2);
+        else if (S.K <= 96)
+            SCPS_PRODUCE(24, 2);
+        else
+            SCPS_PRODUCE(32, 2);
+    } else {
+        if (S.K <= 16)
+            SCPS_PRODUCE(8, 1);
+        else if (S.K <= 32)
+            SCPS_PRODUCE(16, 1);
+        else if (S.K <= 40)
+            SCPS_PRODUCE(20, 1);
+        else if (S.K <= 52)
+            SCPS_PRODUCE(26, 1);
+        else
+            SCPS_PRODUCE(32, 1);
+    }
+#undef SCPS_PRODUCE
 }
 
-template <bool BIG>
+template <bool MASK>
+__device__ __forceinline__ void scps_bias_consume_any(const KParams &P, const SysDesc &S, const ScpsItem &it,
+                                                      const int lane, const int pw, const int n_slots, const int kb,
+                                                      const int ke, BiasLds &L, float fi[][3], float fj[][3]) {
+#define SCPS_CONSUME(SPW) scps_bias_consume<MASK, SPW>(P, S, it, lane, pw, kb, ke, L, fi, fj)
+    static_assert(BIAS_SPW == 4, "one case per number of slots");
+    switch (n_slots) {
+    case 0: SCPS_CONSUME(0); break;
+    case 1: SCPS_CONSUME(1); break;
+    case 2: SCPS_CONSUME(2); break;
+    case 3: SCPS_CONSUME(3); break;
+    default: SCPS_CONSUME(4); break;
+    }
+#undef SCPS_CONSUME
+}
+
+template <bool BIG, bool HALF>
 __global__ __launch_bounds__(BIAS_WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_scps_bias(
     const KParams P, const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
     const ScpsGroup *__restrict__ groups, const ScpsItem *__restrict__ items, const int n_items,
     const float4 *__restrict__ xs, const float *__restrict__ coef, const double *__restrict__ csum, const int kmax,
     const int ksplit, double *__restrict__ acc) {
     __shared__ BiasLds L;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int cur = -1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int cur = -1, nrep = 0;
     SysDesc S;
     // work unit t: a range of the sub-steps of item t / ksplit (ksplit > 1
     // when there are too few items to fill the chip), in whole chunks
@@ -1199,7 +1300,7 @@ __global__ __launch_bounds__(BIAS_WG) __attribute__((amdgpu_waves_per_eu(3, 3)))
         if (it.group != cur) {
             cur = it.group;
             const ScpsGroup *gp = groups + cur;
-            const int nrep = gp->nrep;
+            nrep = gp->nrep;
             S = sysd[gp->sys];
             for (int e = tid; e < KMAX / 2 * 64; e += BIAS_WG) {
                 const int kk = e >> 6, l = e & 63, sl = l & 31, k = 2 * kk + (l >> 5);
@@ -1227,10 +1328,15 @@ __global__ __launch_bounds__(BIAS_WG) __attribute__((amdgpu_waves_per_eu(3, 3)))
         for (int m = 0; m < BIAS_SPW; ++m)
 #pragma unroll
             for (int c = 0; c < 3; ++c) fi[m][c] = fj[m][c] = 0.f;
-        if (it.flags & TILE_MASK)
-            scps_bias_dispatch<true, BIG>(P, S, it, lane, wave, kb, ke, L, fi, fj);
-        else
-            scps_bias_dispatch<false, BIG>(P, S, it, lane, wave, kb, ke, L, fi, fj);
+        if (wave < BIAS_NMW) {
+            scps_bias_produce_any<BIG, HALF>(S, it, lane, wave, kb, ke, L);
+        } else {
+            const int pw = wave - BIAS_NMW, n_slots = (nrep - pw + BIAS_NPW - 1) / BIAS_NPW;   // <= 0: none
+            if (it.flags & TILE_MASK)
+                scps_bias_consume_any<true>(P, S, it, lane, pw, max(n_slots, 0), kb, ke, L, fi, fj);
+            else
+                scps_bias_consume_any<false>(P, S, it, lane, pw, max(n_slots, 0), kb, ke, L, fi, fj);
+        }
         if (wave < BIAS_NMW || kb == ke) continue;
         // after sub-steps kb .. ke-1 lane l holds the j-side partials of particle (l + ke) mod 64
         const int jo = J * 64 + ((lane + ke) & 63);
@@ -1331,21 +1437,40 @@ hipError_t launch_scps_eff(const SysDesc *sysd, const RepDesc *reps, const ScpsG
 }
 
 hipError_t launch_scps_bias(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
-                            const ScpsItem *items, int n_items, int max_frames, const float4 *xs, const float *coef,
-                            const double *csum, int kmax, double *acc, hipStream_t st) {
+                            const ScpsItem *items, int n_items, int max_frames, int max_group, const float4 *xs,
+                            const float *coef, const double *csum, int kmax, double *acc, hipStream_t st) {
     if (n_items == 0) return hipSuccess;
     if (max_frames < 1 || max_frames > KMAX || max_frames > kmax) return hipErrorInvalidValue;
-    // one workgroup per compute unit (LDS); too few items for 256 (small
-    // systems) split each tile's sub-steps over up to 8 workgroups
+    // one workgroup per compute unit (LDS).  Each tile's sub-steps are split over
+    // up to 8 workgroups (whole chunks) where that shortens the pass: rounds of
+    // 256 units, each 64 / ks sub-steps and the staging and first chunk of a unit
+    // (about 7 sub-steps more).  15 tiles take 8 ranges, and 300 tiles, whose
+    // second round of 44 left the chip idle, 4 (20 replicas x 72
+    // frames: 168 -> 142 us).
     int ks = 1;
-    while (ks < 8 && n_items * ks * 2 <= 256) ks *= 2;
+    double best = 1e30;
+    for (int k = 1; k <= 8; k *= 2) {
+        const double t = std::ceil(n_items * (double)k / 256.0) * (64.0 / k + 7.0);
+        if (t < 0.97 * best) {
+            best = t;
+            ks = k;
+        }
+    }
     const int grid = std::min(n_items * ks, 256);
-    if (max_frames > 64)
-        hipLaunchKernelGGL(k_scps_bias<true>, dim3(grid), dim3(BIAS_WG), 0, st, P, sysd, reps, groups, items, n_items,
-                           xs, coef, csum, kmax, ks, acc);
-    else
-        hipLaunchKernelGGL(k_scps_bias<false>, dim3(grid), dim3(BIAS_WG), 0, st, P, sysd, reps, groups, items,
-                           n_items, xs, coef, csum, kmax, ks, acc);
+#define SCPS_LAUNCH(BIG, HALF)                                                                                     \
+    hipLaunchKernelGGL((k_scps_bias<BIG, HALF>), dim3(grid), dim3(BIAS_WG), 0, st, P, sysd, reps, groups, items, n_items, \
+                       xs, coef, csum, kmax, ks, acc)
+    if (max_frames > 64) {
+        if (max_group <= 16)
+            SCPS_LAUNCH(true, true);
+        else
+            SCPS_LAUNCH(true, false);
+    } else if (max_group <= 16) {
+        SCPS_LAUNCH(false, true);
+    } else {
+        SCPS_LAUNCH(false, false);
+    }
+#undef SCPS_LAUNCH
     return hipGetLastError();
 }
 
