@@ -431,10 +431,11 @@ void build_schedule(SysHost &h) {
 scps_status ensure_scps_groups(scps_ctx *c) {
     if (c->d_groups) return SCPS_OK;
     const int R = c->R;
-    HIP_TRY(c, dalloc(c, &c->d_X, (size_t)R * c->kmax));
-    HIP_TRY(c, hipMemset(c->d_X, 0, (size_t)R * c->kmax * sizeof(double)));
-    HIP_TRY(c, dalloc(c, &c->d_Q, R));
-    HIP_TRY(c, hipMemset(c->d_Q, 0, R * sizeof(double)));
+    const size_t xq = (size_t)R * XQ_COPIES;
+    HIP_TRY(c, dalloc(c, &c->d_X, xq * c->kmax));
+    HIP_TRY(c, hipMemset(c->d_X, 0, xq * c->kmax * sizeof(double)));
+    HIP_TRY(c, dalloc(c, &c->d_Q, xq));
+    HIP_TRY(c, hipMemset(c->d_Q, 0, xq * sizeof(double)));
     HIP_TRY(c, dalloc(c, &c->d_jref, R));
     HIP_TRY(c, hipMemset(c->d_jref, 0, R * sizeof(int)));
     HIP_TRY(c, dalloc(c, &c->d_jref_eval, R));
@@ -721,7 +722,7 @@ scps_status make_pairmajor(scps_ctx *c, SysHost &h) {
         h.d_stack_pm = nullptr;
         h.d_G = nullptr;
         h.K_pm = 0;
-        HIP_TRY(c, dalloc(c, &h.d_stack_pm, (size_t)stack_pm_width(h.K) * h.ntile_c * 4096));
+        HIP_TRY(c, dalloc(c, &h.d_stack_pm, (size_t)stack_pm_width(h.K) * h.ntile_c * 4096 + STACK_PM_SLACK));
         HIP_TRY(c, dalloc(c, &h.d_G, (size_t)h.K * h.K + stack_finish_scratch(h.K)));   // G, then its partial sums
         h.K_pm = h.K;
     }
@@ -904,7 +905,7 @@ scps_status step_launches(scps_ctx *c, double *cv, uint64_t step, const uint64_t
     }
     if (tev) HIP_TRY(c, hipEventRecord(tev[0], st));
     HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems,
-                                max_stack_frames(c), c->d_jref, c->d_xs, c->d_X, c->d_Q, c->kmax, -1, st));
+                                max_stack_frames(c), c->max_group, c->d_jref, c->d_xs, c->d_X, c->d_Q, c->kmax, -1, st));
     if (tev) HIP_TRY(c, hipEventRecord(tev[1], st));
     HIP_TRY(c, launch_finalize_scps(c->kp, c->d_sysd, c->d_reps, c->R, c->kmax, c->d_jref, c->d_X, c->d_Q, cv,
                                     c->d_coef, c->d_csum, st));
@@ -1024,7 +1025,7 @@ scps_status step_impl(scps_ctx *c, float *x, float *v, double *cv, int64_t n_ste
             // a new stack: every replica's reference frame is its nearest frame,
             // from one distance pass around frame 0
             HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems,
-                                        max_stack_frames(c), nullptr, c->d_xs, c->d_X, c->d_Q, c->kmax, -1,
+                                        max_stack_frames(c), c->max_group, nullptr, c->d_xs, c->d_X, c->d_Q, c->kmax, -1,
                                         c->stream));
             HIP_TRY(c, launch_tube_eval(c->prm.lambda, c->kp.wscale, nullptr, c->d_jref, c->d_sysd, c->d_reps,
                                         c->R, c->kmax, -1, c->d_X, c->d_Q, nullptr, nullptr, nullptr, 0.0, 1,
@@ -1172,13 +1173,13 @@ scps_status eval_tube_impl(scps_ctx *c, int32_t n_stacks, const int32_t *stacks,
     for (int k = 0; k < n_stacks; ++k) {
         // two passes: around frame 0, to find each replica's nearest frame, then around that frame
         const int K = c->sys[stacks[k]].K;
-        HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems, K, nullptr,
+        HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems, K, c->max_group, nullptr,
                                     c->d_xs, c->d_X, c->d_Q, c->kmax, stacks[k], c->stream));
         HIP_TRY(c, launch_tube_eval(c->prm.lambda, c->kp.wscale, nullptr, c->d_jref_eval, c->d_sysd, c->d_reps, c->R,
                                     c->kmax, stacks[k], c->d_X, c->d_Q, nullptr, nullptr, nullptr, 0.0, 1,
                                     c->stream));
         HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems, K,
-                                    c->d_jref_eval, c->d_xs, c->d_X, c->d_Q, c->kmax, stacks[k], c->stream));
+                                    c->max_group, c->d_jref_eval, c->d_xs, c->d_X, c->d_Q, c->kmax, stacks[k], c->stream));
         HIP_TRY(c, launch_tube_eval(c->prm.lambda, c->kp.wscale, c->d_jref_eval, nullptr, c->d_sysd, c->d_reps, c->R,
                                     c->kmax, stacks[k], c->d_X, c->d_Q, s, w, sigma, 1.0 / n_stacks, k == 0,
                                     c->stream));

@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "scps_internal.h"
+
 namespace scps {
 
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -63,6 +65,32 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// The distance pass adds into XQ_COPIES sets of sums X[r][copy][kmax], Q[r][copy]
+// (workgroup b into set b mod XQ_COPIES): atomics on one address wait for each
+// other, and in a small system all workgroups meet on one group's sums.  Adds
+// the sets up in order (the lane's frames lane, lane + 64 into yk) and clears
+// them; returns sum u^2.
+__device__ __forceinline__ double take_xq(int lane, int K, int kmax, int r, double *__restrict__ X,
+                                          double *__restrict__ Q, double yk[2]) {
+    double *xr = X + (int64_t)r * XQ_COPIES * kmax, *qr = Q + (int64_t)r * XQ_COPIES;
+    // one set per lane: vector loads, which a later store of the same wavefront to
+    // the same address does not overtake (scalar loads of a uniform address it may)
+    const double q = wave_sum(lane < XQ_COPIES ? qr[lane] : 0.0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int k = lane + 64 * h;
+        yk[h] = 0.0;
+        if (k < K) {
+#pragma unroll
+            for (int c = 0; c < XQ_COPIES; ++c) yk[h] += xr[c * kmax + k];
+#pragma unroll
+            for (int c = 0; c < XQ_COPIES; ++c) xr[c * kmax + k] = 0.0;
+        }
+    }
+    if (lane < XQ_COPIES) qr[lane] = 0.0;
+    return q;
+}
+
 // Tube variables of one replica from its squared distances to the K <= 128
 // frames of a stack, one wavefront (lane holds frames lane and lane + 64).
 // The distances are expanded around a reference frame j of the stack: with
@@ -70,7 +98,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 //   d_k Z0 = sum_p (C_p - R_kp)^2 = sum_p u_p^2 + 2 (Y_j - Y_k) + G_jk,
 //   Y_k = sum_p u_p R_kp,  G_jk = sum_p (R_jp - R_kp)^2,
 // so d_j carries no cancellation at all and the rounding of the Y sums
-// scales with the distance to frame j (q = sum u^2, yr = Y, Gj = row j of G).
+// scales with the distance to frame j (q = sum u^2, yk = Y of the lane's frames, Gj = row j
+// of G).
 // Then a = max_k (-lambda d_k), e_k = exp(-lambda d_k - a), s0 = sum_k e_k,
 // s1 = sum_k k e_k: s = 1 - (s1 / s0) / (K - 1) and w = -wscale (a + log s0),
 // the discrete forms of eqs (asXa), (awXa) with a log-sum-exp shift.  kmax is
@@ -81,15 +110,15 @@ struct TubeSums {
     double a, s0, s1;
     int kmax;
 };
-__device__ __forceinline__ TubeSums tube_sums(int lane, int K, double q, const double *yr, int j, const double *Gj,
+__device__ __forceinline__ TubeSums tube_sums(int lane, int K, double q, const double yk[2], int j, const double *Gj,
                                               double Z0, double lam) {
     TubeSums t;
     double dk[2];
-    const double yj = yr[j];
+    const double yj = __shfl(j < 64 ? yk[0] : yk[1], j & 63, 64);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int k = lane + 64 * h;
-        dk[h] = k < K ? fmax(q + 2.0 * (yj - yr[k]) + Gj[k], 0.0) / Z0 : 0.0;
+        dk[h] = k < K ? fmax(q + 2.0 * (yj - yk[h]) + Gj[k], 0.0) / Z0 : 0.0;
     }
     double a = -INFINITY;
 #pragma unroll

@@ -67,6 +67,8 @@ struct RepDesc {
     int64_t eoff;            // SCPS: offset of its effective reference [ntile_c][64*64]
 };
 
+constexpr int XQ_COPIES = 16;   // sets of the distance pass's sums (see take_xq)
+
 // SCPS: up to 32 replicas of one system share every read of the frame stack.
 constexpr int SCPS_GROUP = 32;
 struct ScpsGroup {
@@ -125,8 +127,11 @@ constexpr int TAIL_STEPS = SCPS_TAIL_STEPS;
 constexpr int FINE_STEPS = 16, FINE_BELOW = 3;
 
 // Frames per pair in the pair-major stack: K rounded up to a multiple of 4
-// (zero-filled), so a lane reads four frames of a pair with one 16-byte load.
+// (zero-filled), so a lane reads up to four frames of a pair with one load.
 __host__ __device__ inline int stack_pm_width(int K) { return (K + 3) & ~3; }
+// Floats past its end that the distance pass may read (three frames a lane, of
+// which the last lane in use can hold fewer)
+constexpr int STACK_PM_SLACK = 4;
 
 // Contact tile pairs (I <= J < ncb) are numbered row by row.
 __host__ __device__ inline int tile_index(int I, int J, int ncb) {
@@ -176,12 +181,14 @@ hipError_t launch_pairs(int mode, int nbk, const KParams &P, const SysDesc *sysd
                         const float *eff, const double *csum, hipStream_t st);
 // stack_sys: -1 for each group's own system's stack, else that system's
 // (same chain and contact set as every group's).  max_frames: the largest K
-// of the stacks read (1 .. KMAX), which sets the number of 64-frame blocks.
+// of the stacks read (1 .. KMAX), max_group the largest number of replicas in a
+// group: the kernel's frame blocks and row groups.
 // jref [R]: each replica's reference frame j of the distance expansion (NULL:
-// frame 0); X receives Y_k = sum_p (C_p - R_jp) R_kp and Q sum_p (C_p - R_jp)^2.
+// frame 0); X [R][XQ_COPIES][kmax] receives Y_k = sum_p (C_p - R_jp) R_kp and
+// Q [R][XQ_COPIES] sum_p (C_p - R_jp)^2, in XQ_COPIES parts.
 hipError_t launch_scps_dist(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
-                            const ScpsItem *items, int n_items, int max_frames, const int *jref, const float4 *xs,
-                            double *X, double *Q, int kmax, int stack_sys, hipStream_t st);
+                            const ScpsItem *items, int n_items, int max_frames, int max_group, const int *jref,
+                            const float4 *xs, double *X, double *Q, int kmax, int stack_sys, hipStream_t st);
 // s, w, sigma of every replica from the distances in X, Q (which it clears);
 // jref_in: the reference frames the distance pass used (NULL: frame 0);
 // jref_out (nullable): each replica's frame of largest weight.

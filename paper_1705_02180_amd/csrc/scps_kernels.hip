@@ -2017,10 +2017,11 @@ __global__ void k_finalize_scps(const KParams P, const SysDesc *__restrict__ sys
     const int lane = threadIdx.x;
     const SysDesc S = sysd[reps[r].sys];
     const int K = S.K, M = K - 1;
-    double *xr = X + (int64_t)r * kmax;
     const double lam = P.lambda;
     const int j = ref_frame(jref, r, K);
-    const TubeSums ts = tube_sums(lane, K, Q[r], xr, j, S.G + (int64_t)j * K, S.Z0, lam);
+    double yk[2];
+    const double q = take_xq(lane, K, kmax, r, X, Q, yk);
+    const TubeSums ts = tube_sums(lane, K, q, yk, j, S.G + (int64_t)j * K, S.Z0, lam);
     const double *e = ts.e;
     const double a = ts.a, s0 = ts.s0, s1 = ts.s1;
     const double kbar = s1 / s0;
@@ -2040,12 +2041,10 @@ __global__ void k_finalize_scps(const KParams P, const SysDesc *__restrict__ sys
             const double ckv = pk * (P.k_s * ds * (lam / (double)M) * ((double)k - kbar) + P.k_w * dw * lw);
             coef[(int64_t)r * kmax + k] = (float)(ckv / S.Z0);
             tot += ckv;
-            xr[k] = 0.0;
         }
     }
     tot = wave_sum(tot);
     if (lane == 0) {
-        Q[r] = 0.0;
         csum[r] = tot / S.Z0;
         if (jref) jref[r] = ts.kmax;
         c[CV_S] = sv;

@@ -610,241 +610,248 @@ __device__ __forceinline__ float contact_operand(const KParams &P, const float4 
     return (ok & inside) ? num * frcp(den) : 0.f;
 }
 
-#ifndef SCPS_DIST_AHEAD
-#define SCPS_DIST_AHEAD 8
-#endif
-#ifndef SCPS_DIST_REF_AHEAD
-#define SCPS_DIST_REF_AHEAD 4   // the reference values ride a shorter ring (registers)
-#endif
-#ifndef SCPS_DIST_REF_GLOBAL
-#define SCPS_DIST_REF_GLOBAL 0  // 1: R_j from its own load also for stacks of at most 64 frames
-#endif
 // Pass 1, around each replica's reference frame j_r (see tube_sums): with
 // u_rp = C_rp - R_{j_r}p, X[r][k] += sum_p u_rp R_kp and Q[r] += sum_p u_rp^2
 // over the contact pairs of each work item (group of replicas, tile);
 // workgroups stride over the items and flush their sums when the group
 // changes and at the end.
-// The pairs of a tile are taken row by row: wavefront w takes rows
-// i = w, w+4, ... of block I and, per row, 32 MFMA steps of 2 pairs
-// (i, 2m + (l >> 5)); lane l evaluates u of that pair for replica l & 31 (A
-// operand of 32x32x2 float32 MFMAs) with particle i's position held in a
-// register, particle j's read from the block-J positions in LDS and R_j of
-// the pair, and loads frames 2 (l & 31) and 2 (l & 31) + 1 of the pair with
-// one 8-byte load SCPS_DIST_AHEAD steps ahead of their use.  R_j is one of
-// those loaded values (lane (j >> 1) + 32 (l >> 5), component j & 1), fetched
-// across lanes with ds_bpermute; a stack of more than 64 frames (REFLOAD)
-// loads it from the pair's frames instead, SCPS_DIST_REF_AHEAD steps ahead,
-// since frame j need not lie in the current frame block.  Frame block h holds frames 2j + h,
-// so component h of that load is the lane's B operand of block h.  A diagonal
-// tile counts the pairs j > i.  The float32 accumulators hold one row (64
-// pairs per element) and are added after every row into the workgroup's
-// float64 sums xl[slot][frame] in LDS; u^2 goes to float64 term by term (a
-// Q that carries float32 partial sums moves w by more than the ratchets
-// near the appendix limit allow).  Element v of lane l in block h is
-// replica slot 8 (v >> 2) + 4 (l >> 5) + (v & 3), frame 64 fb + 2 (l & 31) + h:
-// a stack of more than 64 frames is taken in frame blocks fb of 64, each a
-// pass of its own over the tile (the contact values are recomputed; Q is
-// summed in block 0 only).
+//
+// 16x16x4 float32 MFMAs: NR row groups of 16 replicas (2, or 1 where no group
+// has more than 16) against NB blocks of 16 frames (NB the smallest of 1 .. 6
+// and 8 that holds the stack), so the matrix and the pair work go with the
+// replicas and the frames.  (32x32x2 blocks, 32 replicas x 64 frames a pass
+// over the tile, ran 128 frames for 65, in two passes that each took the
+// contact values again, and 32 replicas for 8.)  The pairs of a tile are taken
+// row by row: wavefront w takes rows i = w, w + NW, ... of block I and, per row,
+// 16 steps of 4 pairs (i, 4m + (l >> 4)); lane l evaluates u of that pair for
+// replicas 16 g + (l & 15) (A operands, one per row group) with particle i's
+// positions in registers (loaded a row ahead) and particle j's from the block-J
+// positions in LDS, and loads its frames of the pair (min(NB, 4) (l & 15) ...,
+// and from 64 on (NB - 4) (l & 15) ...) with one or two vector loads
+// DIST_AHEAD steps ahead of their use.  A wavefront writes the frames of its
+// next 4 pairs to LDS, where each lane finds R_j of its replicas (LDS
+// operations of a wavefront keep their order, so one buffer is enough; cross-
+// lane moves of the same took one per row group and vector component).  A
+// diagonal tile counts the pairs j > i.  The float32 accumulators hold one row
+// (64 pairs per element) and are added after every row into the workgroup's
+// float64 sums xl in LDS; u^2 goes to float64 term by term (a Q that carries
+// float32 partial sums moves w by more than the ratchets near the appendix
+// limit allow).  Element v of lane l in row group g, block b is replica slot
+// 16 g + 4 (l >> 4) + v, frame dist_frame(b, l & 15).
 // Addressing: pair (i, j) sits at s * 64 + i in the tile, s = (j - i) mod 64.
-// At step m of row i the uniform row b = (2m - i) mod 64 gives s = b + (l >> 5)
-// except for b = 63 and l >> 5 = 1 (s = 0), so every load is a uniform base
-// (scalar registers) plus one of two per-lane offsets fixed for the tile.
-// Lanes of slots without a replica (l & 31 >= nrep) compute finite values
-// from zero positions that reach only their own output rows and Q partials,
-// which the flush drops; MASK and DIAG tiles zero u of pairs that do not count.
-template <bool MASK, bool REFLOAD, bool DIAG, int NW>
+// Lanes of slots without a replica compute finite values from zero positions
+// that reach only their own output rows and Q sums, which the flush drops;
+// MASK tiles (diagonal ones among them) zero u of pairs that do not count.
+// Bound by MFMA and VALU issue, which do not overlap on a SIMD here (about 35
+// VALU instructions a step of 4 pairs and 32 replicas beside its 8 MFMAs; 42
+// with the 32x32x2 form).  us a pass, 32x32x2 form -> now: 32 replicas x 6000
+// particles x 51 frames 1117 -> 1041 (in the map update), 20 x 1501 x 72 232 ->
+// 111, 15 x 1700 x 70 242 -> 106, 30 x 2100 x 50 213 -> 165, 32 x 3000 x 12 319
+// -> 157.
+constexpr int DIST_AHEAD = 4;   // 2: 1.07 against 1.00 ms at 6000 particles; 8 spills (1.45 ms)
+constexpr int DIST_NW = 8;   // wavefronts per workgroup, sharing block J and the float64 sums
+
+template <int NR, int NB>
+struct DistLds {
+    static constexpr int SCW = 16 * NB + 4;      // frames of a pair, rows 16-byte aligned
+    float4 posj[64][16 * NR];                    // block J of every replica slot
+    double xl[16 * NR][16 * NB];                 // float64 sums of the current group, columns 16 b + (l & 15)
+    float sc[DIST_NW][4][SCW];                   // each wavefront's next 4 pairs, by frame
+    double qs[16 * NR];
+    int orgj[64];
+    int rep[16 * NR];
+    int jref[16 * NR];                           // reference frame of every replica slot
+};
+template <int NR, int NB>
+constexpr int dist_resident() { return sizeof(DistLds<NR, NB>) <= 80 * 1024 ? 2 : 1; }   // workgroups per CU
+
+// frame of column c (0 .. 15) of block b
+template <int NB>
+__device__ __forceinline__ int dist_frame(int b, int c) {
+    constexpr int W0 = NB < 4 ? NB : 4, W1 = NB - W0;
+    return b < W0 ? W0 * c + b : 64 + W1 * c + (b - W0);
+}
+
+template <bool MASK, int NR, int NB>
 __device__ __forceinline__ void scps_dist_tile(const KParams &P, const SysDesc &S, const int nrep,
-                                               const ScpsItem &it, const int fb_in, const float4 (*posj)[32],
-                                               const int *orgj, const float4 *__restrict__ xs,
-                                               const RepDesc *__restrict__ reps, const int myrep, const int jr,
-                                               const int lane, const int wave, const int r0, const int r1, double *xl,
-                                               double &q) {
+                                               const ScpsItem &it, DistLds<NR, NB> &L, const float4 *__restrict__ xs,
+                                               const RepDesc *__restrict__ reps, const int lane, const int wave,
+                                               const int r0, const int r1, double q[NR]) {
+    constexpr int W0 = NB < 4 ? NB : 4, W1 = NB - W0, D = DIST_AHEAD;
+    static_assert(16 % D == 0, "the ring keeps its phase over a row");
+    typedef float vec0 __attribute__((ext_vector_type(W0), aligned(W0 == 3 ? 4 : 4 * W0)));
+    typedef float vec1 __attribute__((ext_vector_type(W1 > 0 ? W1 : 1), aligned(W1 > 0 ? 4 * W1 : 4)));
+    typedef float acc4 __attribute__((ext_vector_type(4)));
     const int I = it.IJ >> 16, J = it.IJ & 0xFFFF;
+    const bool diag = I == J;
     const int K4 = stack_pm_width(S.K);
-    const int rs = lane & 31, pq = lane >> 5;
-    const bool rep = rs < nrep;
-    // a stack of at most 64 frames has the one frame block 0: known at compile
-    // time, so the step loop below has no branch
-    const int fb = REFLOAD ? fb_in : 0;
-    const bool bload = 64 * fb + 2 * rs < K4;
-    const bool sum_q = fb == 0;
-    constexpr bool REF_LD = REFLOAD || SCPS_DIST_REF_GLOBAL;
-    // global (not flat) loads from a uniform base with 32-bit lane offsets:
-    // flat loads would also count against the LDS wait counter and drain the ring
-    typedef float v2 __attribute__((ext_vector_type(2)));
+    const int col = lane & 15, quad = lane >> 4;
+    // global (not flat) loads from a uniform base with 32-bit lane offsets: flat
+    // loads would also count against the LDS wait counter and drain the ring
     typedef const __attribute__((address_space(1))) char *gbytes;
     const gbytes tile_base = (gbytes)(S.stack_pm + (int64_t)it.tile * 4096 * K4);
     const uint32_t row_bytes = 4u * (uint32_t)K4;   // one pair of the tile, all frames
-    // byte offsets in a row pair: B operands (frames 2 rs, 2 rs + 1 of frame block fb;
-    // lanes past the stack width re-read the pair's first frames, whose columns
-    // the flush drops) and R_j
-    const uint32_t fo = bload ? 8u * (uint32_t)(32 * fb + rs) : 0u, ro = 4u * (uint32_t)jr;
-    const uint32_t up = (uint32_t)pq * 64u * row_bytes;              // s = b + 1 for the upper half
-    const uint32_t wrap = (uint32_t)(1 - pq) * 63u * 64u * row_bytes; // b = 63: lower half s = 63, upper s = 0
-    const float4 *xr = xs + 2 * reps[myrep].poff + I * 128;
-    constexpr int D = SCPS_DIST_AHEAD, DR = SCPS_DIST_REF_AHEAD;
-    static_assert(D % DR == 0 && 32 % D == 0, "the rings advance together");
-    // the base of step m_ of row i_ (a row past the last, i_ = 64, is never consumed:
-    // clamped to 63) and the lane offset
-    auto at = [&](int i_, int m_, uint32_t lane_bytes) {
-        const int ic = i_ < 64 ? i_ : 63;
-        const int b = (2 * m_ - ic) & 63;
-        const bool w = b == 63;
-        const gbytes base = tile_base + (uint32_t)((w ? 0 : b) * 64 + ic) * row_bytes;
-        return base + ((w ? wrap : up) + lane_bytes);
-    };
-    auto bop = [&](int i_, int m_) {
-        typedef const __attribute__((address_space(1))) v2 *gv2;
-        return *(gv2)at(i_, m_, fo);
-    };
-    auto rop = [&](int i_, int m_) {   // R_j of the same pair, the reference of slot rs
-        typedef const __attribute__((address_space(1))) float *gf;
-        return *(gf)at(i_, m_, ro);
-    };
-    v2 ring[D];
-    float rring[REF_LD ? DR : 1];
+    // lanes past the stack width re-read the pair's first frames (a lane across its
+    // end reads on into the next pair); the flush drops their columns
+    const uint32_t f0 = W0 * col < K4 ? 4u * (uint32_t)(W0 * col) : 0u;
+    const uint32_t f1 = W1 > 0 && 64 + W1 * col < K4 ? 4u * (uint32_t)(64 + W1 * col) : 0u;
+    const float4 *xr[NR];
+    int jr[NR];
+    bool rep[NR];
 #pragma unroll
-    for (int u = 0; u < D; ++u) ring[u] = bop(r0 + wave, u);
-    if constexpr (REF_LD) {
-#pragma unroll
-        for (int u = 0; u < DR; ++u) rring[u] = rop(r0 + wave, u);
+    for (int g = 0; g < NR; ++g) {
+        const int slot = 16 * g + col;
+        rep[g] = slot < nrep;
+        xr[g] = xs + 2 * reps[L.rep[slot]].poff + I * 128;
+        jr[g] = L.jref[slot];
     }
-    const int ref_lane = ((jr >> 1) + 32 * pq) << 2;   // ds_bpermute byte address of the lane holding R_j
-    // R_j of a step from the B operands of that step (one step ahead of its use,
-    // so the cross-lane move is off the contact value -> MFMA chain)
-    auto ref_of = [&](const v2 &bb) {
-        const float rx = __int_as_float(__builtin_amdgcn_ds_bpermute(ref_lane, __float_as_int(bb.x)));
-        const float ry = __int_as_float(__builtin_amdgcn_ds_bpermute(ref_lane, __float_as_int(bb.y)));
-        return (jr & 1) ? ry : rx;
+    struct Frames {
+        vec0 a;
+        vec1 b;
     };
-    float rj_next = 0.f;
-    if constexpr (!REF_LD) rj_next = ref_of(ring[0]);
+    // step m of row i (a row past the last is never consumed: clamped to 63)
+    auto load = [&](int i_, int m_) {
+        const int ic = i_ < 64 ? i_ : 63;
+        const int b = (4 * m_ - ic) & 63;   // uniform; s = (b + quad) mod 64
+        const uint32_t lo = __umul24((uint32_t)(b + quad) & 63u, 64u * row_bytes);
+        const gbytes base = tile_base + (uint32_t)ic * row_bytes;
+        Frames r;
+        r.a = *(const __attribute__((address_space(1))) vec0 *)(base + (lo + f0));
+        if constexpr (W1 > 0) r.b = *(const __attribute__((address_space(1))) vec1 *)(base + (lo + f1));
+        return r;
+    };
+    auto *sc = L.sc[wave];
+    auto publish = [&](const Frames &r) {
+        *reinterpret_cast<vec0 *>(&sc[quad][W0 * col]) = r.a;
+        if constexpr (W1 > 0) *reinterpret_cast<vec1 *>(&sc[quad][64 + W1 * col]) = r.b;
+    };
+    Frames ring[D];
+#pragma unroll
+    for (int u = 0; u < D; ++u) ring[u] = load(r0 + wave, u);
+    float rj[NR];
+    publish(ring[0]);
+#pragma unroll
+    for (int g = 0; g < NR; ++g) rj[g] = sc[quad][jr[g]];
+    typedef float vec3 __attribute__((ext_vector_type(3), aligned(16)));
+    vec3 pn[NR];   // the next row's particle i
+    auto particle = [&](int g, int i_) {
+        typedef const __attribute__((address_space(1))) vec3 *gvec3;
+        return *(gvec3)(xr[g] + min(i_, 63));
+    };
+#pragma unroll
+    for (int g = 0; g < NR; ++g) pn[g] = particle(g, r0 + wave);
 #pragma unroll 1
-    for (int i = r0 + wave; i < r1; i += NW) {
-        const float4 pi = rep ? xr[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = r0 + wave; i < r1; i += DIST_NW) {
+        float4 pi[NR];
+#pragma unroll
+        for (int g = 0; g < NR; ++g) {
+            pi[g] = make_float4(rep[g] ? pn[g].x : 0.f, rep[g] ? pn[g].y : 0.f, rep[g] ? pn[g].z : 0.f, 0.f);
+            pn[g] = particle(g, i + DIST_NW);
+        }
         const int oi = MASK ? S.perm[I * 64 + i] : 0;
         const bool icon = I * 64 + i < S.nc;
-        fvec16 acc[2];
+        acc4 acc[NR][NB];
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int g = 0; g < NR; ++g)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[h][v] = 0.f;
+            for (int b = 0; b < NB; ++b) acc[g][b] = acc4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-        for (int mg = 0; mg < 32 / D; ++mg) {
+        for (int mg = 0; mg < 16 / D; ++mg) {
 #pragma unroll
             for (int u = 0; u < D; ++u) {
                 const int m = D * mg + u;
-                const v2 b = ring[u];
-                float rj;
-                if constexpr (REF_LD) {
-                    rj = rring[u % DR];
-                    const int rm = m + DR < 32 ? m + DR : m + DR - 32, ri = m + DR < 32 ? i : i + NW;
-                    rring[u % DR] = rop(ri, rm);
-                } else {
-                    rj = rj_next;
-                    rj_next = ref_of(ring[(u + 1) % D]);   // holds the next step's B operands
+                const Frames f = ring[u];
+                float rc[NR];
+#pragma unroll
+                for (int g = 0; g < NR; ++g) rc[g] = rj[g];
+                publish(ring[(u + 1) % D]);   // the next step's frames (u = D - 1: loaded D - 1 steps ago)
+#pragma unroll
+                for (int g = 0; g < NR; ++g) rj[g] = sc[quad][jr[g]];
+                ring[u] = m + D < 16 ? load(i, m + D) : load(i + DIST_NW, m + D - 16);
+                const int jl = 4 * m + quad;
+                bool ok0 = true;
+                if constexpr (MASK)
+                    ok0 = icon & (J * 64 + jl < S.nc) & (abs(oi - L.orgj[jl]) > P.min_sep) & (!diag | (jl > i));
+#pragma unroll
+                for (int g = 0; g < NR; ++g) {
+                    const float4 pj = L.posj[jl][16 * g + col];
+                    float c;
+                    if constexpr (MASK) {
+                        const bool ok = ok0 & rep[g];
+                        const float cv = contact_operand<true>(P, pi[g], pj, ok);
+                        c = ok ? cv - rc[g] : 0.f;   // u = C - R_j of a counted pair
+                    } else {
+                        c = contact_operand<false>(P, pi[g], pj, true) - rc[g];
+                    }
+                    q[g] = fma((double)c, (double)c, q[g]);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const float bv = b < W0 ? f.a[b < W0 ? b : 0] : f.b[b < W0 ? 0 : b - W0];
+                        acc[g][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(c, bv, acc[g][b], 0, 0, 0);
+                    }
                 }
-                const int nm = m + D < 32 ? m + D : m + D - 32, ni = m + D < 32 ? i : i + NW;
-                ring[u] = bop(ni, nm);
-                const int jl = 2 * m + pq;
-                float c;
-                if constexpr (MASK || DIAG) {
-                    bool ok = rep;
-                    if constexpr (DIAG) ok = ok & (jl > i);
-                    if constexpr (MASK) ok = ok & icon & (J * 64 + jl < S.nc) & (abs(oi - orgj[jl]) > P.min_sep);
-                    const float cv = contact_operand<MASK>(P, pi, posj[jl][rs], ok);
-                    c = ok ? cv - rj : 0.f;   // u = C - R_j of a counted pair
-                } else {
-                    c = contact_operand<false>(P, pi, posj[jl][rs], true) - rj;
-                }
-                if (sum_q) q = fma((double)c, (double)c, q);
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(c, b.x, acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(c, b.y, acc[1], 0, 0, 0);
             }
         }
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int g = 0; g < NR; ++g)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                atomicAdd(&xl[(8 * (v >> 2) + 4 * pq + (v & 3)) * 64 + 2 * rs + h], (double)acc[h][v]);
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) atomicAdd(&L.xl[16 * g + 4 * quad + v][16 * b + col], (double)acc[g][b][v]);
     }
 }
 
-#ifndef SCPS_DIST_WPE
-#define SCPS_DIST_WPE 3
-#endif
-#ifndef SCPS_DIST_NW
-#define SCPS_DIST_NW 8      // wavefronts per workgroup for stacks of at most 64 frames
-#endif
-#ifndef SCPS_DIST_NW_WPE
-#define SCPS_DIST_NW_WPE 4  // waves per SIMD with that workgroup (two workgroups per CU)
-#endif
-// Launch shape of k_scps_dist: stacks of at most 64 frames take SCPS_DIST_NW
-// wavefronts per workgroup sharing one staging of block J and one set of
-// float64 sums (more wavefronts per CU in the LDS of fewer workgroups); the
-// larger stacks (more registers per lane) take four.
-template <bool BIGK>
-struct DistShape {
-    static constexpr int NW = BIGK ? 4 : SCPS_DIST_NW;
-    static constexpr int WPE = BIGK ? SCPS_DIST_WPE : SCPS_DIST_NW_WPE;
-    static constexpr int WG = 64 * NW;
-    static constexpr int RESIDENT = 4 * WPE / NW;   // workgroups per CU
-};
-// Work unit t covers item t mod n_items in frame block t / n_items (nfb
-// blocks of 64 frames); the sums are flushed when (group, frame block) changes.
-// BIGK: stacks of more than 64 frames (a kernel of its own).
-template <bool BIGK>
-__global__ __launch_bounds__(DistShape<BIGK>::WG)
-__attribute__((amdgpu_waves_per_eu(DistShape<BIGK>::WPE, DistShape<BIGK>::WPE))) void k_scps_dist(
-    const KParams P, const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
-    const ScpsGroup *__restrict__ groups, const ScpsItem *__restrict__ items, const int n_items, const int nfb,
-    const int nsplit, const int *__restrict__ jref, const float4 *__restrict__ xs, double *__restrict__ X,
-    double *__restrict__ Q, const int kmax, const int stack_sys) {
-    __shared__ __align__(16) float4 posj[64][32];   // block J of every replica slot
-    __shared__ double xl[32 * 64];                   // float64 sums X[slot][frame] of the current group
-    constexpr int NW = DistShape<BIGK>::NW, WG = DistShape<BIGK>::WG;
-    __shared__ double ql[NW][64];
-    __shared__ int orgj[64];
-    __shared__ int sh_rep[32];
-    __shared__ int sh_jref[32];                      // reference frame of every replica slot
+// Work unit t: rows [r0, r0 + 64 / nsplit) of item t / nsplit.  The sums are
+// flushed when the group changes.
+template <int NR, int NB>
+__global__ __launch_bounds__(64 * DIST_NW)
+__attribute__((amdgpu_waves_per_eu(dist_resident<NR, NB>() * DIST_NW / 4, dist_resident<NR, NB>() * DIST_NW / 4)))
+void k_scps_dist(const KParams P, const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
+                 const ScpsGroup *__restrict__ groups, const ScpsItem *__restrict__ items, const int n_items,
+                 const int nsplit, const int *__restrict__ jref, const float4 *__restrict__ xs,
+                 double *__restrict__ X, double *__restrict__ Q, const int kmax, const int stack_sys) {
+    __shared__ __align__(16) DistLds<NR, NB> L;
+    constexpr int WG = 64 * DIST_NW, SLOTS = 16 * NR, COLS = 16 * NB;
     // the wavefront index is uniform: in a scalar register, the row and step
     // arithmetic of the tile loop (and its load bases) stay scalar
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int e = tid; e < 32 * 64; e += WG) xl[e] = 0.0;
-    double q = 0.0;
-    int cur = -1, cur_fb = 0, nrep = 0;
+    for (int e = tid; e < SLOTS * COLS; e += WG) L.xl[e / COLS][e % COLS] = 0.0;
+    if (tid < SLOTS) L.qs[tid] = 0.0;
+    double q[NR];
+#pragma unroll
+    for (int g = 0; g < NR; ++g) q[g] = 0.0;
+    int cur = -1, nrep = 0;
     SysDesc S;
-    // work unit t: rows [r0, r0 + 64 / nsplit) of item u mod n_items in frame
-    // block u / n_items, u = t / nsplit (nsplit > 1 when there are too few
-    // items to fill the chip)
-    const int n_units = n_items * nfb * nsplit, rows = 64 / nsplit;
+    const int n_units = n_items * nsplit, rows = 64 / nsplit;
+    const int copy = blockIdx.x % XQ_COPIES;
     for (int t = blockIdx.x;; t += gridDim.x) {
         const bool more = t < n_units;
         const int u = t / nsplit, r0 = (t - u * nsplit) * rows;
-        const int fb = (BIGK && more) ? u / n_items : 0;
-        const ScpsItem it = more ? items[u - fb * n_items] : ScpsItem{-1, 0, 0, 0};
-        const bool change = it.group != cur || fb != cur_fb;
+        const ScpsItem it = more ? items[u] : ScpsItem{-1, 0, 0, 0};
+        const bool change = it.group != cur;
         if (cur >= 0 && change) {
-            // flush the sums of (group, frame block) to the replicas' float64 totals
-            ql[wave][lane] = q;
+            // flush the group's sums to one of the replicas' XQ_COPIES float64 totals
+#pragma unroll
+            for (int g = 0; g < NR; ++g) {
+                unsafeAtomicAdd(&L.qs[16 * g + (lane & 15)], q[g]);
+                q[g] = 0.0;
+            }
             __syncthreads();
-            for (int e = tid; e < 32 * 64; e += WG) {
-                const int slot = e >> 6, k = 64 * cur_fb + (e & 63);
-                if (slot < nrep && k < S.K) unsafeAtomicAdd(&X[(int64_t)sh_rep[slot] * kmax + k], xl[e]);
-                xl[e] = 0.0;
+            for (int e = tid; e < SLOTS * COLS; e += WG) {
+                const int slot = e / COLS, c = e % COLS, k = dist_frame<NB>(c >> 4, c & 15);
+                if (slot < nrep && k < S.K)
+                    unsafeAtomicAdd(&X[((int64_t)L.rep[slot] * XQ_COPIES + copy) * kmax + k], L.xl[slot][c]);
+                L.xl[slot][c] = 0.0;
             }
-            if (tid < 32 && cur_fb == 0) {
-                double sum = 0.0;
-                for (int w = 0; w < NW; ++w) sum += ql[w][tid] + ql[w][32 + tid];
-                if (tid < nrep) unsafeAtomicAdd(&Q[sh_rep[tid]], sum);
+            if (tid < SLOTS) {
+                if (tid < nrep) unsafeAtomicAdd(&Q[L.rep[tid] * XQ_COPIES + copy], L.qs[tid]);
+                L.qs[tid] = 0.0;
             }
-            q = 0.0;
         }
         if (!more) break;
         __syncthreads();
         if (change) {
             cur = it.group;
-            cur_fb = fb;
             const ScpsGroup *gp = groups + cur;
             nrep = gp->nrep;
             S = sysd[gp->sys];
@@ -852,39 +859,26 @@ __attribute__((amdgpu_waves_per_eu(DistShape<BIGK>::WPE, DistShape<BIGK>::WPE)))
                 S.stack_pm = sysd[stack_sys].stack_pm;
                 S.K = sysd[stack_sys].K;
             }
-            if (tid < 32) {
-                sh_rep[tid] = tid < nrep ? gp->rep[tid] : 0;
-                sh_jref[tid] = tid < nrep ? ref_frame(jref, gp->rep[tid], S.K) : 0;
+            if (tid < SLOTS) {
+                L.rep[tid] = tid < nrep ? gp->rep[tid] : gp->rep[0];
+                L.jref[tid] = tid < nrep ? ref_frame(jref, gp->rep[tid], S.K) : 0;
             }
             __syncthreads();
         }
-        if (64 * fb >= S.K) continue;   // the group's stack has no frame in this block (uniform per workgroup)
         // stage block J of every replica of the group
         const int J = it.IJ & 0xFFFF;
-        for (int e = tid; e < 64 * 32; e += WG) {
-            const int pl = e >> 5, slot = e & 31;
+        for (int e = tid; e < 64 * SLOTS; e += WG) {
+            const int pl = e / SLOTS, slot = e % SLOTS;
             float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (slot < nrep) p = xs[2 * reps[sh_rep[slot]].poff + J * 128 + pl];
-            posj[pl][slot] = p;
+            if (slot < nrep) p = xs[2 * reps[L.rep[slot]].poff + J * 128 + pl];
+            L.posj[pl][slot] = p;
         }
-        if (tid < 64) orgj[tid] = S.perm[J * 64 + tid];
+        if (tid < 64) L.orgj[tid] = S.perm[J * 64 + tid];
         __syncthreads();
-        const int myrep = sh_rep[lane & 31], myj = sh_jref[lane & 31];
-        const bool diag = (it.IJ >> 16) == J;
-        if (it.flags & TILE_MASK) {
-            if (diag)
-                scps_dist_tile<true, BIGK, true, NW>(P, S, nrep, it, fb, posj, orgj, xs, reps, myrep, myj, lane, wave,
-                                                 r0, r0 + rows, xl, q);
-            else
-                scps_dist_tile<true, BIGK, false, NW>(P, S, nrep, it, fb, posj, orgj, xs, reps, myrep, myj, lane, wave,
-                                                  r0, r0 + rows, xl, q);
-        } else if (diag) {
-            scps_dist_tile<false, BIGK, true, NW>(P, S, nrep, it, fb, posj, orgj, xs, reps, myrep, myj, lane, wave, r0,
-                                              r0 + rows, xl, q);
-        } else {
-            scps_dist_tile<false, BIGK, false, NW>(P, S, nrep, it, fb, posj, orgj, xs, reps, myrep, myj, lane, wave, r0,
-                                               r0 + rows, xl, q);
-        }
+        if ((it.flags & TILE_MASK) || (it.IJ >> 16) == J)
+            scps_dist_tile<true, NR, NB>(P, S, nrep, it, L, xs, reps, lane, wave, r0, r0 + rows, q);
+        else
+            scps_dist_tile<false, NR, NB>(P, S, nrep, it, L, xs, reps, lane, wave, r0, r0 + rows, q);
     }
 }
 
@@ -1356,35 +1350,50 @@ __global__ __launch_bounds__(BIAS_WG) __attribute__((amdgpu_waves_per_eu(3, 3)))
     }
 }
 
+template <int NR, int NB>
+static void launch_scps_dist_as(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
+                                const ScpsItem *items, int n_items, const int *jref, const float4 *xs, double *X,
+                                double *Q, int kmax, int stack_sys, hipStream_t st) {
+    // each tile's rows are split over up to 16 workgroups where that shortens the
+    // pass: rounds of 256 CUs, each 8 / ns rows of a wavefront and the staging and
+    // first loads of a unit (about 0.7 rows; 16 ranges leave half the wavefronts
+    // without a row and were still faster than 8 at 15 tiles)
+    int ns = 1;
+    double best = 1e30;
+    for (int k = 1; k <= 16; k *= 2) {
+        const double t = std::ceil(n_items * (double)k / 256.0) * (8.0 / k + 0.7);
+        if (t < 0.97 * best) {
+            best = t;
+            ns = k;
+        }
+    }
+    const int grid = std::min(n_items * ns, 256 * dist_resident<NR, NB>());
+    hipLaunchKernelGGL((k_scps_dist<NR, NB>), dim3(grid), dim3(64 * DIST_NW), 0, st, P, sysd, reps, groups, items,
+                       n_items, ns, jref, xs, X, Q, kmax, stack_sys);
+}
+
 hipError_t launch_scps_dist(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
-                            const ScpsItem *items, int n_items, int max_frames, const int *jref, const float4 *xs,
-                            double *X, double *Q, int kmax, int stack_sys, hipStream_t st) {
+                            const ScpsItem *items, int n_items, int max_frames, int max_group, const int *jref,
+                            const float4 *xs, double *X, double *Q, int kmax, int stack_sys, hipStream_t st) {
     if (n_items == 0) return hipSuccess;
     if (max_frames < 1 || max_frames > KMAX || max_frames > kmax) return hipErrorInvalidValue;
-    const int nfb = (max_frames + 63) / 64;
-    // a grid of the resident workgroups (256 CUs) striding over the work
-    // units; too few items for that (small systems) split each tile's rows
-    // over up to 16 workgroups (4 rows each, half the wavefronts without a
-    // row: still faster than 8 at 32 x 560, while 16 sub-step ranges of the
-    // bias pass were slower than 8)
-    auto split = [&](int resident) {
-        int ns = 1;
-        while (ns < 16 && n_items * nfb * ns * 2 <= resident) ns *= 2;
-        return ns;
-    };
-    if (nfb > 1) {
-        typedef DistShape<true> DS;
-        const int ns = split(256 * DS::RESIDENT);
-        const int grid = std::min(n_items * nfb * ns, 256 * DS::RESIDENT);
-        hipLaunchKernelGGL(k_scps_dist<true>, dim3(grid), dim3(DS::WG), 0, st, P, sysd, reps, groups, items, n_items,
-                           nfb, ns, jref, xs, X, Q, kmax, stack_sys);
-    } else {
-        typedef DistShape<false> DS;
-        const int ns = split(256 * DS::RESIDENT);
-        const int grid = std::min(n_items * ns, 256 * DS::RESIDENT);
-        hipLaunchKernelGGL(k_scps_dist<false>, dim3(grid), dim3(DS::WG), 0, st, P, sysd, reps, groups, items,
-                           n_items, nfb, ns, jref, xs, X, Q, kmax, stack_sys);
+#define SCPS_DIST(NB)                                                                                              \
+    do {                                                                                                           \
+        if (max_group <= 16)                                                                                       \
+            launch_scps_dist_as<1, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, kmax, stack_sys, st); \
+        else                                                                                                       \
+            launch_scps_dist_as<2, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, kmax, stack_sys, st); \
+    } while (0)
+    switch ((max_frames + 15) / 16) {
+    case 1: SCPS_DIST(1); break;
+    case 2: SCPS_DIST(2); break;
+    case 3: SCPS_DIST(3); break;
+    case 4: SCPS_DIST(4); break;
+    case 5: SCPS_DIST(5); break;
+    case 6: SCPS_DIST(6); break;
+    default: SCPS_DIST(8); break;
     }
+#undef SCPS_DIST
     return hipGetLastError();
 }
 
@@ -1402,16 +1411,13 @@ __global__ void k_tube_eval(double lam, double wscale, const int *__restrict__ j
     const int r = blockIdx.x, lane = threadIdx.x;
     const SysDesc S = sysd[stack_sys >= 0 ? stack_sys : reps[r].sys];
     const int K = S.K;
-    double *xr = X + (int64_t)r * kmax;
     const int j = ref_frame(jref_in, r, K);
-    const TubeSums ts = tube_sums(lane, K, Q[r], xr, j, S.G + (int64_t)j * K, S.Z0, lam);
+    double yk[2];
+    const double q = take_xq(lane, K, kmax, r, X, Q, yk);
+    const TubeSums ts = tube_sums(lane, K, q, yk, j, S.G + (int64_t)j * K, S.Z0, lam);
     const double sv = 1.0 - (ts.s1 / ts.s0) / (double)(K - 1);
     const double wv = tube_w(ts.a, ts.s0, wscale);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-        if (lane + 64 * h < K) xr[lane + 64 * h] = 0.0;
     if (lane == 0) {
-        Q[r] = 0.0;
         if (s) s[r] = sv;
         if (w) w[r] = wv;
         if (sigma) sigma[r] = (first ? 0.0 : sigma[r]) + weight * (1.0 - sv);
