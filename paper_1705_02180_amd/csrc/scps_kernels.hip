@@ -338,8 +338,7 @@ __device__ __forceinline__ void tile_dispatch2(const int flags, const int kb, co
 // MASK tile evaluates the per-pair predicates only on the groups whose
 // sub-step bits are set in mk.  The
 // lane's reference values are loaded D sub-steps ahead of their use into a
-// ring of registers: D = 4 groups in the per-step kernels, whose maps stream
-// from HBM, one group where the map is cache-resident (persistent kernel).
+// ring of registers.
 // Outputs: fi[0..2] nonbonded, fi[3..5] contact gradient (i side); fj
 // likewise for the j particle lane l holds at the end (see jflush_at); zt:
 // this lane's z partial.
@@ -1516,7 +1515,13 @@ __global__ __launch_bounds__(256) void k_pairs(const KParams P, const SysDesc *_
     }
     const bool diag = tf & TF_DIAG;
     const int kb = tile_kbeg(diag), ke = tile_kend(diag);
-    tile_dispatch<MODE, NBK, 4 * SCPS_PAIR_GROUP>(tf, kb, ke, it.mask, P, lane, A, shpos[wave], shorg[wave],
+    // groups of sub-steps unrolled, whose reference values are in flight (when there
+    // are any): more of them cost registers and instruction cache, and the other
+    // wavefronts of the SIMD cover the loads.  us a pass with 1 / 2 / 4 groups:
+    // z and gradient (64 x 3000) 263 / 272 / 317, z alone 202 / 199 / 256, forces
+    // (128 uneven chains) 349 / 336 / 362, nonbonded alone (32 x 6000) - / 618 / 552
+    constexpr int PAIR_UNROLL = MODE == PM_NB ? 4 : MODE == PM_ZG ? 1 : 2;
+    tile_dispatch<MODE, NBK, PAIR_UNROLL * SCPS_PAIR_GROUP>(tf, kb, ke, it.mask, P, lane, A, shpos[wave], shorg[wave],
                                                   S.nc - J * 64, rt, cs, fi, fj, zt);
     const int jo = J * 64 + jflush_at(lane, ke);
     double *ar = acc + 6 * rd.poff;
