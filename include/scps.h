@@ -384,7 +384,9 @@ scps_status scps_autotune(scps_ctx *ctx, const float *x, const float *v, const d
  *   path 1: the per-step path (param ignored; the only path of an SCPS
  *           context);
  *   path 2: the packed persistent kernel, param = wavefronts per workgroup
- *           (1 .. 8; every chain of at most 64 particles).
+ *           (1 .. 8; every chain of at most 64 particles).  Batches of at most
+ *           2048 replicas, of chains of 8 particles or more, give each replica a
+ *           wavefront of its own.
  * Without a call or a tuning, chains of at most 48 particles (at most 64
  * from 2048 replicas up) run packed with four wavefronts per workgroup and
  * longer ones on the persistent kernel where they fit (256 threads per

@@ -49,18 +49,26 @@ __device__ __forceinline__ float ldg(const float *p, int64_t i) {
 // Three standard normals for (particle, replica, step).  The uniforms are odd
 // multiples of 2^-24, exact in float32; Box-Muller runs in float32 (logf,
 // sqrtf, sincospif: within a few ulp of the float64 transform).
-__device__ __forceinline__ void normals3(const KParams &P, uint32_t atom, uint32_t rep, uint64_t step,
-                                         double &g0, double &g1, double &g2) {
+__device__ __forceinline__ void normals3f(const KParams &P, uint32_t atom, uint32_t rep, uint64_t step, float &g0,
+                                          float &g1, float &g2) {
     uint32_t c[4] = {atom, rep, (uint32_t)step, (uint32_t)(step >> 32)};
     philox4x32_10(c, P.seed_lo, P.seed_hi);
     const float r01 = sqrtf(-2.f * logf(unit_open_f(c[0])));
     const float r23 = sqrtf(-2.f * logf(unit_open_f(c[2])));
     float sn, cs;
     sincospif(2.f * unit_open_f(c[1]), &sn, &cs);
-    g0 = (double)(r01 * cs);
-    g1 = (double)(r01 * sn);
+    g0 = r01 * cs;
+    g1 = r01 * sn;
     sincospif(2.f * unit_open_f(c[3]), &sn, &cs);
-    g2 = (double)(r23 * cs);
+    g2 = r23 * cs;
+}
+__device__ __forceinline__ void normals3(const KParams &P, uint32_t atom, uint32_t rep, uint64_t step,
+                                         double &g0, double &g1, double &g2) {
+    float f0, f1, f2;
+    normals3f(P, atom, rep, step, f0, f1, f2);
+    g0 = (double)f0;
+    g1 = (double)f1;
+    g2 = (double)f2;
 }
 
 // ---------------------------------------------------------------------------
@@ -1350,6 +1358,340 @@ __global__ __launch_bounds__(512) void k_rmd_packed(const KParams P, const SysDe
     }
 }
 
+// ---------------------------------------------------------------------------
+// the same chains in a small batch: one wavefront per replica
+// ---------------------------------------------------------------------------
+// A batch that leaves most SIMDs without a wavefront is bound by the latency of
+// one step in one wavefront (3.0 us for 20 particles: 10 dependent partner steps,
+// 12 cross-lane moves of the segment sum, then the noise).  Here a replica has a
+// wavefront to itself, C = 64 / n lanes per particle: lane c n + a takes the
+// partner steps k = c + 1, c + 1 + C, ... of particle a, WIDE_U of them side by side
+// with j-side partials of their own that move WIDE_U C lanes at a time within the copy; the copies' forces then meet in a
+// tree, z is summed over the wavefront by DPP, the noise is drawn before the
+// pair phase (its arithmetic covers the position reads), and the first copy's
+// lanes update.  us per step of 16 replicas, packed ->
+// one wavefront per replica: n = 8 1.90 -> 1.55, 10 2.13 -> 1.53, 20 2.98 -> 1.69, 32 4.21 ->
+// 2.31, 48 5.63 -> 4.88.
+template <int CTRL>
+__device__ __forceinline__ double dpp_shifted(double v) {
+    // lanes without a source get 0
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+// Sum over the wavefront in a fixed order, uniform: rows of 16 by shifts, then
+// row totals broadcast to the next rows; lane 63 holds the total.
+__device__ __forceinline__ double wave_total(double v) {
+    v += dpp_shifted<0x111>(v);   // row_shr 1, 2, 4, 8
+    v += dpp_shifted<0x112>(v);
+    v += dpp_shifted<0x114>(v);
+    v += dpp_shifted<0x118>(v);
+    // row_bcast 15 into rows 1 and 3, row_bcast 31 into rows 2 and 3
+    {
+        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x142, 0xA, 0xF, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x142, 0xA, 0xF, false);
+        v += __hiloint2double(hi, lo);
+    }
+    {
+        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x143, 0xC, 0xF, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x143, 0xC, 0xF, false);
+        v += __hiloint2double(hi, lo);
+    }
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+__device__ __forceinline__ float permute_f32(int from, float v) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v)));
+}
+
+// Partner steps of a lane: ceil(floor(n / 2) / (64 / n)) rounded up to whole
+// groups of WIDE_U, at most 32.
+constexpr int WIDE_U = 2;   // 4: 89 us against 88 at 20 particles, 92 against 77 at 10, 260 against 244 at 48
+__host__ __device__ inline int wide_steps(int n) {
+    const int copies = 64 / n, steps = (n / 2 + copies - 1) / copies;
+    return (steps + WIDE_U - 1) / WIDE_U * WIDE_U;
+}
+// LDS of one wavefront: positions, chain indices, the chain predecessors, the
+// noise and the lane's native-map value at every partner step.
+constexpr size_t WIDE_WAVE_LDS = 64 * (sizeof(float4) + 2 * sizeof(int)) + (3 + 32) * 64 * sizeof(float);
+
+template <int NBK>
+__global__ __launch_bounds__(512) void k_rmd_wide(const KParams P, const SysDesc *__restrict__ sysd,
+                                                  const RepDesc *__restrict__ reps, const int R,
+                                                  float *__restrict__ x, float *__restrict__ v,
+                                                  double *__restrict__ cv, const int64_t n_steps, const uint64_t step0,
+                                                  const int record_every, float *__restrict__ frames,
+                                                  const int64_t frame_stride, int *__restrict__ flags) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned char *wl = smem + (size_t)wave * WIDE_WAVE_LDS;
+    float4 *posl = reinterpret_cast<float4 *>(wl);       // [64]
+    int *orgl = reinterpret_cast<int *>(posl + 64);       // [64]
+    int *prevl = orgl + 64;                                // [64]
+    float *noise = reinterpret_cast<float *>(prevl + 64); // [3][64]
+    float *refl = noise + 3 * 64;                          // [32][64]
+    const int r = (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
+    if (r >= R) return;   // the whole wavefront: nothing below crosses wavefronts
+    const RepDesc rd = reps[r];
+    const SysDesc S = sysd[rd.sys];
+    const int n = S.n, copies = 64 / n, steps = wide_steps(n);
+    const int c = lane / n, a = lane - c * n;
+    const bool in = c < copies, lead = c == 0;
+    float *xr = x + 3 * rd.off;
+    float *vr = v ? v + 3 * rd.off : nullptr;
+    int o = lane, nxt = -1;
+    float4 p = pad_position(lane);
+    float vel[3] = {0.f, 0.f, 0.f};
+    double inv_m = 1.0;
+    if (in) {
+        o = S.perm[a];
+        p = make_float4(xr[o], xr[n + o], xr[2 * n + o], S.charge[a]);
+        if (vr && lead) {
+            vel[0] = vr[o];
+            vel[1] = vr[n + o];
+            vel[2] = vr[2 * n + o];
+        }
+        inv_m = 1.0 / (double)S.mass[a];
+        nxt = S.bond_next[a];
+    }
+    const float qp = P.dh_pref * p.w;
+    if (lead) {
+        orgl[a] = o;
+        prevl[a] = -1;
+    }
+    wave_lds_sync();
+    if (lead && nxt >= 0) prevl[nxt] = a;
+    wave_lds_sync();
+    const int prv = lead ? prevl[a] : -1;
+    // step s of this lane is partner step k = c + 1 + copies s, met with b = (a + k)
+    // mod n (for even n, at k = n/2 only by the particles a < n/2): bit s of nbmask /
+    // cmask counts the pair in the nonbonded sum / in the contact set
+    uint32_t nbmask = 0u, cmask = 0u;
+    for (int t = 0; t < steps; ++t) {
+        const int k = c + 1 + copies * t;
+        float rv = 0.f;
+        if (in && k <= (n >> 1) && (2 * k < n || a < (n >> 1))) {
+            const int b = a + k < n ? a + k : a + k - n;
+            const int sep = abs(o - orgl[b]);
+            if (sep > P.nb_excl) nbmask |= 1u << t;
+            if (a < S.nc && b < S.nc) {
+                if (sep > P.min_sep) cmask |= 1u << t;
+                rv = S.ref[((b - a) & 63) * 64 + a];
+            }
+        }
+        refl[t * 64 + lane] = rv;
+    }
+    // WIDE_U steps at a time, each with j-side partials of its own (their moves are
+    // independent): the partners' indices at steps 0 .. WIDE_U - 1 and their stride, the
+    // lane the partials come from (WIDE_U copies further in the same copy), and the
+    // lanes that hold this particle's partials after the last group
+    const int cm = WIDE_U * copies % n;
+    int b0[WIDE_U], home_from[WIDE_U];
+    const int rot_from = (in ? c * n + (a + cm) % n : lane) << 2;
+#pragma unroll
+    for (int u = 0; u < WIDE_U; ++u) {
+        b0[u] = in ? (a + c + 1 + copies * u) % n : 0;
+        int home = in ? (a - (c + 1) - copies * (steps - WIDE_U + u)) % n : 0;
+        home = home < 0 ? home + n : home;
+        home_from[u] = (in ? c * n + home : lane) << 2;
+    }
+    double zm = cv[(int64_t)r * CV_STRIDE + CV_ZM];
+    double z_last = cv[(int64_t)r * CV_STRIDE + CV_Z];
+    double eb_last = cv[(int64_t)r * CV_STRIDE + CV_EB];
+    double tsum = 0.0;
+    bool bad = false;
+    int phase = 0;
+    const double c1 = P.c1;
+    const double mob = P.dt * inv_m / P.gamma;
+    const double amp = P.integrator == 0 ? sqrt(2.0 * P.kT * mob) : sqrt((1.0 - c1 * c1) * P.kT * inv_m);
+    for (int64_t m = 0;; ++m) {
+        if (record_every > 0 && frames && (m % record_every) == 0 && lead) {
+            float *fr = frames + (m / record_every) * frame_stride + 3 * rd.off;
+            fr[o] = p.x;
+            fr[n + o] = p.y;
+            fr[2 * n + o] = p.z;
+        }
+        if (m == n_steps) break;
+        if (lead) posl[a] = p;
+        wave_lds_sync();
+        if (in) p = posl[a];
+        if (phase == 0) {   // the copies draw the noise of this and the next copies - 1 steps
+            float g0, g1, g2;
+            normals3f(P, (uint32_t)o, P.rep_base + (uint32_t)r, step0 + (uint64_t)(m + c), g0, g1, g2);
+            noise[lane] = g0;
+            noise[64 + lane] = g1;
+            noise[128 + lane] = g2;
+            wave_lds_sync();
+        }
+        float gf[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) gf[k] = noise[64 * k + (lead ? phase * n + a : 0)];
+        phase = phase + 1 < copies ? phase + 1 : 0;
+        float fn[3] = {0.f, 0.f, 0.f}, fg[3] = {0.f, 0.f, 0.f}, jn[WIDE_U][3], jg[WIDE_U][3];
+        float zt = 0.f;
+        int b[WIDE_U];
+#pragma unroll
+        for (int u = 0; u < WIDE_U; ++u) {
+            b[u] = b0[u];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) jn[u][k] = jg[u][k] = 0.f;
+        }
+        for (int t = 0; t < steps; t += WIDE_U) {
+            float4 pj[WIDE_U];
+            float rv[WIDE_U];
+#pragma unroll
+            for (int u = 0; u < WIDE_U; ++u) {
+                pj[u] = posl[b[u]];
+                rv[u] = refl[(t + u) * 64 + lane];
+                b[u] += cm;
+                b[u] = b[u] >= n ? b[u] - n : b[u];
+            }
+            if (t > 0) {
+#pragma unroll
+                for (int u = 0; u < WIDE_U; ++u)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        if constexpr (NBK != 0) jn[u][k] = permute_f32(rot_from, jn[u][k]);
+                        jg[u][k] = permute_f32(rot_from, jg[u][k]);
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < WIDE_U; ++u) {
+                float dx, dy, dz;
+                const float r2 = pair_r2(p, pj[u], dx, dy, dz);
+                if constexpr (NBK != 0) {
+                    const bool nbon = (((nbmask >> (t + u)) & 1u) != 0u) & (!P.has_cut_nb | (r2 <= P.r_cut_nb2));
+                    const float fs = nb_scalar<NBK>(P, r2, qp, pj[u].w);
+                    const float f = nbon ? fs : 0.f;
+                    fn[0] = fmaf(f, dx, fn[0]);
+                    fn[1] = fmaf(f, dy, fn[1]);
+                    fn[2] = fmaf(f, dz, fn[2]);
+                    jn[u][0] = fmaf(-f, dx, jn[u][0]);
+                    jn[u][1] = fmaf(-f, dy, jn[u][1]);
+                    jn[u][2] = fmaf(-f, dz, jn[u][2]);
+                }
+                const bool con = ((cmask >> (t + u)) & 1u) != 0u;
+                const bool inside = !P.has_cut | (r2 <= P.r_cut2);   // beyond a cutoff C = 0 (R still counts)
+                const float q = r2 * P.inv_r0sq;
+                const float q2 = q * q;
+                const float tq = q + q2;
+                const float num = 1.f + tq;
+                const float den = fmaf(q2, tq, num);
+                const float inv_den = inside ? frcp(den) : 0.f;
+                float diff = num * inv_den - rv[u];
+                diff = con ? diff : 0.f;
+                zt = fmaf(diff, diff, zt);
+                const float poly = fmaf(q, fmaf(q, fmaf(q, P.cp[0], P.cp[1]), P.cp[2]), P.cp[3]);
+                const float g = (diff * (q2 * inv_den)) * (poly * inv_den);
+                fg[0] = fmaf(g, dx, fg[0]);
+                fg[1] = fmaf(g, dy, fg[1]);
+                fg[2] = fmaf(g, dz, fg[2]);
+                jg[u][0] = fmaf(-g, dx, jg[u][0]);
+                jg[u][1] = fmaf(-g, dy, jg[u][1]);
+                jg[u][2] = fmaf(-g, dz, jg[u][2]);
+            }
+        }
+        // the j-side partials to their particle's lane, then the copies' sums to the
+        // first copy (a tree over c)
+#pragma unroll
+        for (int u = 0; u < WIDE_U; ++u)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                if constexpr (NBK != 0) fn[k] += permute_f32(home_from[u], jn[u][k]);
+                fg[k] += permute_f32(home_from[u], jg[u][k]);
+            }
+        for (int w = 1; w < copies; w *= 2) {
+            const bool take = in && (c & (2 * w - 1)) == 0 && c + w < copies;
+            const int from = (take ? lane + w * n : lane) << 2;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                if constexpr (NBK != 0) {
+                    const float u = permute_f32(from, fn[k]);
+                    fn[k] += take ? u : 0.f;
+                }
+                const float u = permute_f32(from, fg[k]);
+                fg[k] += take ? u : 0.f;
+            }
+        }
+        // ---- ratchet, eq (FrMD): z_m updated before the force is used ----
+        const double z = wave_total((double)zt);
+        zm = fmin(zm, z);
+        const double dzr = z - zm;
+        const double scale = -P.k_R * dzr;
+        z_last = z;
+        eb_last = 0.5 * P.k_R * dzr * dzr;
+        // ---- Langevin update, float64 per particle ----------------------
+        if (lead) {
+            double F[3] = {(double)fn[0], (double)fn[1], (double)fn[2]};
+            if (P.has_bond) {
+                // both bonds of the particle, each exactly opposite to what its other end
+                // takes; a bond that does not exist is one with the particle itself,
+                // whose force is not a number, and is left out
+                double f[3], h[3];
+                bond_force(P, p, posl[nxt >= 0 ? nxt : a], f);
+                bond_force(P, p, posl[prv >= 0 ? prv : a], h);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    F[k] += nxt >= 0 ? f[k] : 0.0;
+                    F[k] += prv >= 0 ? h[k] : 0.0;
+                }
+            }
+            double fb2 = 0.0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const double fb = scale * (double)fg[k];
+                F[k] += fb;
+                fb2 = fma(fb, fb, fb2);
+            }
+            tsum = fma(fb2, inv_m, tsum);
+            double X[3] = {(double)p.x, (double)p.y, (double)p.z};
+            if (P.integrator == 0) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) X[k] += mob * F[k] + amp * (double)gf[k];
+            } else {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    double u = (double)vel[k] + P.dt * F[k] * inv_m;
+                    X[k] += 0.5 * P.dt * u;
+                    u = c1 * u + amp * (double)gf[k];
+                    X[k] += 0.5 * P.dt * u;
+                    vel[k] = (float)u;
+                }
+            }
+            p = make_float4((float)X[0], (float)X[1], (float)X[2], p.w);
+            bad |= !(isfinite(p.x) && isfinite(p.y) && isfinite(p.z));
+        }
+        wave_lds_sync();
+    }
+    if (lead) {
+        xr[o] = p.x;
+        xr[n + o] = p.y;
+        xr[2 * n + o] = p.z;
+        if (vr) {
+            vr[o] = vel[0];
+            vr[n + o] = vel[1];
+            vr[2 * n + o] = vel[2];
+        }
+        if (bad) flags[r] = 1;
+    }
+    // bias functional: T += dt sum_steps sum_i |F_bias,i|^2 / (m_i gamma)
+    const double tt = wave_total(lead ? tsum : 0.0);
+    if (lane == 0 && n_steps > 0) {
+        cv[(int64_t)r * CV_STRIDE + CV_Z] = z_last;
+        cv[(int64_t)r * CV_STRIDE + CV_ZM] = zm;
+        cv[(int64_t)r * CV_STRIDE + CV_EB] = eb_last;
+        cv[(int64_t)r * CV_STRIDE + CV_T] += P.dt / P.gamma * tt;
+    }
+}
+
+// One wavefront per replica for chains of at least 8 particles (shorter ones have
+// more copies than the tree over them gains) while it gives a SIMD (256 CUs x 4) at
+// most two.  us for 50 steps, packed / wide: n = 5 82 / 95 (1024 replicas), 10:
+// 112 / 94 (2048), 20: 160 / 112 (2048), 32: 220 / 150 (2048), 45: 1135 / 1157
+// (9000), 48: 345 / 317 (2048), 62: 905 / 911 (5000).
+static bool use_wide(int n_max, int R) { return n_max >= 8 && R <= 2048; }
+
 int packed_width_ok(int n_max) { return n_max >= 2 && n_max <= PACK_WMAX; }
 // Without tuning: chains of up to 48 particles (one replica per wavefront at
 // most 3/4 full still beats a 64-lane persistent tile, which pads to 64), and
@@ -1362,6 +1704,21 @@ hipError_t launch_packed_rmd(int waves, int nbk, const KParams &P, const SysDesc
                              int n_max, float *x, float *v, double *cv, int64_t n_steps, uint64_t step0,
                              int record_every, float *frames, int64_t frame_stride, int *flags, hipStream_t st) {
     if (!packed_width_ok(n_max) || waves < 1 || waves > 8) return hipErrorInvalidValue;
+    if (use_wide(n_max, R)) {
+        const dim3 wide_grid((R + waves - 1) / waves), wide_block(64 * waves);
+        const size_t wide_lds = (size_t)waves * WIDE_WAVE_LDS;
+#define SCPS_LAUNCH(K)                                                                                             \
+    hipLaunchKernelGGL((k_rmd_wide<K>), wide_grid, wide_block, wide_lds, st, P, sysd, reps, R, x, v, cv, n_steps, step0, \
+                       record_every, frames, frame_stride, flags)
+        switch (nbk) {
+        case 0: SCPS_LAUNCH(0); break;
+        case 1: SCPS_LAUNCH(1); break;
+        case 2: SCPS_LAUNCH(2); break;
+        default: SCPS_LAUNCH(3); break;
+        }
+#undef SCPS_LAUNCH
+        return hipGetLastError();
+    }
     const int W = n_max, per_wg = waves * (64 / W);
     const int grid = (R + per_wg - 1) / per_wg;
     const size_t lds = (size_t)waves * packed_wave_lds_bytes(W);
