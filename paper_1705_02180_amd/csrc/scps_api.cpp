@@ -137,11 +137,9 @@ struct scps_ctx {
     int nb_max = 0;
     float4 *d_bounds = nullptr;      // [R][nb_max] block bounding spheres
     float4 *d_xref = nullptr;        // [sumNpad] positions at the last build
-    float *d_bmax = nullptr;         // [sum nb] largest squared displacement per block since then
-    int *d_rebuild = nullptr;        // [R]
+    int *d_rebuild = nullptr;        // [R] a particle has moved more than half the skin since then
     int *d_nl_cnt = nullptr;         // [sumNpad]
     int2 *d_nl = nullptr;            // [sumNpad][NL_CAP]
-    int *d_first_blk = nullptr;      // [R + 1] blocks of 64 particles before each replica
     int *d_first_chunk = nullptr;    // [R + 1] chunks of the list force kernel before each replica
     double *d_zpart_nl = nullptr;    // [chunks] z partials of the list force kernel
     double *d_zbase = nullptr;       // [R] R2total of each replica's system
@@ -654,21 +652,18 @@ scps_status init_impl(const scps_params *params, const scps_topology *topo, int3
             p.exec_mode != SCPS_EXEC_PER_STEP_ALL_TILES && !all.empty();
     if (c->nl) {
         c->r_list = (float)std::max(p.r_cut_contact, p.r_cut_nb) + NL_SKIN;
-        std::vector<int> fb(R + 1, 0), fc(R + 1, 0);
+        std::vector<int> fc(R + 1, 0);
         for (int r = 0; r < R; ++r) {
             const SysHost &h = c->sys[rsys[r]];
             c->nb_max = std::max(c->nb_max, h.nb);
-            fb[r + 1] = fb[r] + h.nb;
             fc[r + 1] = fc[r] + nl_chunks(h.n_pad);
         }
         HIP_TRY(c, dalloc(c, &c->d_bounds, (size_t)R * c->nb_max));
         HIP_TRY(c, dalloc(c, &c->d_xref, c->sumNpad));
-        HIP_TRY(c, dalloc(c, &c->d_bmax, fb[R]));
         HIP_TRY(c, dalloc(c, &c->d_rebuild, R));
+        HIP_TRY(c, hipMemset(c->d_rebuild, 0, R * sizeof(int)));
         HIP_TRY(c, dalloc(c, &c->d_nl_cnt, c->sumNpad));
         HIP_TRY(c, dalloc(c, &c->d_nl, (size_t)c->sumNpad * NL_CAP));
-        HIP_TRY(c, dalloc(c, &c->d_first_blk, R + 1));
-        HIP_TRY(c, hipMemcpy(c->d_first_blk, fb.data(), (R + 1) * sizeof(int), hipMemcpyHostToDevice));
         HIP_TRY(c, dalloc(c, &c->d_first_chunk, R + 1));
         HIP_TRY(c, hipMemcpy(c->d_first_chunk, fc.data(), (R + 1) * sizeof(int), hipMemcpyHostToDevice));
         HIP_TRY(c, dalloc(c, &c->d_zpart_nl, fc[R]));
@@ -1043,15 +1038,18 @@ scps_status step_impl(scps_ctx *c, float *x, float *v, double *cv, int64_t n_ste
         }
         if (!scps && c->nl) {
             // cutoff variant: neighbour lists, rebuilt where a particle moved more than half the skin
-            HIP_TRY(c, launch_nl_update(c->kp, c->d_sysd, c->d_reps, c->R, c->nb_max, c->d_first_blk, c->d_xs,
-                                        c->d_bounds, c->d_xref, c->d_bmax, c->d_rebuild, c->nl_stale, c->d_items_all,
-                                        c->d_first_all, c->r_list, c->d_nl_cnt, c->d_nl, c->d_flags, c->stream));
+            if (m == 0 && !c->nl_stale)
+                HIP_TRY(c, launch_nl_check(c->d_sysd, c->d_reps, c->R, c->n_pad_max, c->d_xs, c->d_xref, c->d_rebuild,
+                                           c->stream));
+            HIP_TRY(c, launch_nl_update(c->kp, c->d_sysd, c->d_reps, c->R, c->nb_max, c->d_xs, c->d_bounds, c->d_xref,
+                                        c->d_rebuild, c->nl_stale, c->d_items_all, c->d_first_all, c->r_list,
+                                        c->d_nl_cnt, c->d_nl, c->d_flags, c->stream));
             c->nl_stale = false;
             HIP_TRY(c, launch_nl_force(c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, c->n_pad_max, c->d_first_chunk,
-                                       c->d_xs, c->d_nl_cnt, c->d_nl, c->d_acc, c->d_zpart_nl, c->stream));
+                                       c->d_xs, c->d_nl_cnt, c->d_nl, c->d_acc, c->d_zpart_nl, c->d_rebuild, c->stream));
             HIP_TRY(c, launch_integrate(c->kp, c->d_sysd, c->d_reps, c->R, c->n_pad_max, c->d_xs, c->d_vs, c->d_acc,
                                         nullptr, cv, step0 + (uint64_t)m, nullptr, c->d_flags, c->stream,
-                                        c->d_first_chunk, c->d_zpart_nl, c->d_zbase));
+                                        c->d_first_chunk, c->d_zpart_nl, c->d_zbase, c->d_xref, c->d_rebuild));
         } else {
             scps_status ss = step_launches(c, cv, step0 + (uint64_t)m, nullptr, true, c->stream);
             if (ss != SCPS_OK) return ss;

@@ -214,20 +214,25 @@ hipError_t launch_stack_finish(int nc, int ncb, int K, int min_sep, const int *p
 // entries per particle, radius (larger cutoff) + NL_SKIN.
 constexpr int NL_CAP = 512;
 constexpr float NL_SKIN = 2.0f;
-// Rebuild the lists of the replicas that need it (force: all of them).
-// first_blk [R+1]: blocks of 64 before each replica; bounds [R][nb_max],
-// xref [sum n_pad], bmax [sum nb], rebuild [R], cnt [sum n_pad],
-// nl [sum n_pad][NL_CAP]; flags[r] = 2 when a list of replica r overflowed.
+// rebuild [R] is set for a replica when a particle has moved more than half the
+// skin from xref [sum n_pad], its position at the last build: by launch_nl_check
+// for positions from outside, by launch_integrate (given xref and rebuild) for the
+// positions it makes; the force kernel clears it.
+hipError_t launch_nl_check(const SysDesc *sysd, const RepDesc *reps, int R, int n_pad_max, const float4 *xs,
+                           const float4 *xref, int *rebuild, hipStream_t st);
+// Rebuild the lists of the replicas with rebuild set (force: all of them).
+// bounds [R][nb_max], cnt [sum n_pad], nl [sum n_pad][NL_CAP]; flags[r] = 2 when a
+// list of replica r overflowed.
 hipError_t launch_nl_update(const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R, int nb_max,
-                            const int *first_blk, const float4 *xs, float4 *bounds, float4 *xref, float *bmax,
-                            int *rebuild, int force, const TileItem *items_all, const int *first_all, float r_list,
-                            int *cnt, int2 *nl, int *flags, hipStream_t st);
+                            const float4 *xs, float4 *bounds, float4 *xref, int *rebuild, int force,
+                            const TileItem *items_all, const int *first_all, float r_list, int *cnt, int2 *nl,
+                            int *flags, hipStream_t st);
 // Particle chunks of the list force kernel for a system of n_pad particles.
 int nl_chunks(int n_pad);
 // Forces (added to acc) and z partials zpart[first_chunk[r] + chunk] over the lists.
 hipError_t launch_nl_force(int nbk, const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R,
                            int n_pad_max, const int *first_chunk, const float4 *xs, const int *cnt, const int2 *nl,
-                           double *acc, double *zpart, hipStream_t st);
+                           double *acc, double *zpart, int *rebuild, hipStream_t st);
 // Per contact tile of a map: sum over its counted pairs of the squared
 // (float32) entries, in float64.
 hipError_t launch_tile_sumsq(int nc, int ncb, int min_sep, const int *perm, const float *tiles, double *out,
@@ -246,7 +251,8 @@ hipError_t launch_integrate(const KParams &P, const SysDesc *sysd, const RepDesc
                             int n_pad_max, float4 *xs, float4 *vs, double *acc,
                             const double *scale, double *cv, uint64_t step, const uint64_t *step_base,
                             int *flags, hipStream_t st, const int *zfirst = nullptr,
-                            const double *zpart = nullptr, const double *zbase = nullptr);
+                            const double *zpart = nullptr, const double *zbase = nullptr,
+                            const float4 *xref = nullptr, int *rebuild = nullptr);
 // *d = v (one thread), in stream order
 hipError_t launch_set_step(uint64_t *d, uint64_t v, hipStream_t st);
 

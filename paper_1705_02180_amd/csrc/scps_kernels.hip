@@ -1998,66 +1998,53 @@ __device__ __forceinline__ double replica_z(const int *__restrict__ first, const
 //   z = sum over all counted pairs of R^2 + sum over listed pairs of C (C - 2R)
 // and each unordered pair is listed twice (once per side).
 
-// Per block b of replica r (one wavefront): its bounding sphere (centroid of
-// its real particles and the largest distance from it) into bounds, and the
-// largest squared displacement of its particles since the last build into
-// bmax[first[r] + b].
-__global__ __launch_bounds__(64) void k_nl_blocks(const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
-                                                  int nb_max, const int *__restrict__ first,
+// A particle beyond half the skin from its position at the last build asks for
+// a rebuild of its replica (so does a position that is not finite).
+__device__ __forceinline__ bool nl_moved(const float4 &p, const float4 &q) {
+    const float dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
+    const float half = 0.5f * NL_SKIN;
+    return !(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) <= half * half);
+}
+
+// The check on positions that no update of this library has checked: the
+// caller's, once a call (between steps k_integrate does it as it moves the
+// particles, which saves reading them again: 5.6 of 10.4 us of list upkeep a
+// step without rebuilds at 32 x 6000).
+__global__ __launch_bounds__(256) void k_nl_check(const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
                                                   const float4 *__restrict__ xs, const float4 *__restrict__ xref,
-                                                  float4 *__restrict__ bounds, float *__restrict__ bmax) {
+                                                  int *__restrict__ rebuild) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, r = blockIdx.y;
+    const RepDesc rd = reps[r];
+    if (i >= sysd[rd.sys].n) return;
+    if (nl_moved(xs[2 * rd.poff + dup_index(i)], xref[rd.poff + i])) rebuild[r] = 1;
+}
+
+// For the replicas that are to be rebuilt (rebuild, or force: all of them), per
+// block b (one wavefront): its bounding sphere (centroid of its real particles and
+// the largest distance from it), its reference positions, and its counts cleared.
+__global__ __launch_bounds__(64) void k_nl_reset(const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
+                                                 int nb_max, const float4 *__restrict__ xs, float4 *__restrict__ xref,
+                                                 float4 *__restrict__ bounds, int force, int *__restrict__ rebuild,
+                                                 int *__restrict__ cnt) {
     const int b = blockIdx.x, r = blockIdx.y, lane = threadIdx.x;
+    if (!force && !rebuild[r]) return;
     const RepDesc rd = reps[r];
     const int n = sysd[rd.sys].n, nb = sysd[rd.sys].nb;
     if (b >= nb) return;
+    if (force && b == 0 && lane == 0) rebuild[r] = 1;
     const int i = b * 64 + lane;
     const bool valid = i < n;
     const float4 p = xs[2 * rd.poff + b * 128 + lane];
-    float m2 = 0.f;
-    if (valid) {
-        const float4 q = xref[rd.poff + i];
-        const float dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
-        m2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        if (!(m2 <= 3.0e38f)) m2 = 3.0e38f;           // a non-finite position forces a rebuild
-    }
-    const double cnt = wave_sum(valid ? 1.0 : 0.0);
-    const double cx = wave_sum(valid ? (double)p.x : 0.0) / cnt;
-    const double cy = wave_sum(valid ? (double)p.y : 0.0) / cnt;
-    const double cz = wave_sum(valid ? (double)p.z : 0.0) / cnt;
+    const double cnt_b = wave_sum(valid ? 1.0 : 0.0);
+    const double cx = wave_sum(valid ? (double)p.x : 0.0) / cnt_b;
+    const double cy = wave_sum(valid ? (double)p.y : 0.0) / cnt_b;
+    const double cz = wave_sum(valid ? (double)p.z : 0.0) / cnt_b;
     const double dx = (double)p.x - cx, dy = (double)p.y - cy, dz = (double)p.z - cz;
     double d2 = valid ? dx * dx + dy * dy + dz * dz : 0.0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        d2 = fmax(d2, __shfl_xor(d2, o, 64));
-        m2 = fmaxf(m2, __shfl_xor(m2, o, 64));
-    }
-    if (lane == 0) {
-        bounds[(int64_t)r * nb_max + b] = make_float4((float)cx, (float)cy, (float)cz, (float)sqrt(d2));
-        bmax[first[r] + b] = m2;
-    }
-}
-
-// Decide per replica whether to rebuild (force, or a displacement beyond
-// NL_SKIN / 2 in any of its blocks); for a rebuild, clear the block's counts
-// and record the reference positions.
-__global__ __launch_bounds__(64) void k_nl_reset(const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
-                                                 const int *__restrict__ first, const float4 *__restrict__ xs,
-                                                 float4 *__restrict__ xref, const float *__restrict__ bmax, int force,
-                                                 int *__restrict__ rebuild, int *__restrict__ cnt) {
-    const int b = blockIdx.x, r = blockIdx.y, lane = threadIdx.x;
-    const RepDesc rd = reps[r];
-    const int nb = sysd[rd.sys].nb;
-    if (b >= nb) return;
-    float d2 = 0.f;
-    for (int q = lane; q < nb; q += 64) d2 = fmaxf(d2, bmax[first[r] + q]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) d2 = fmaxf(d2, __shfl_xor(d2, o, 64));
-    const float half = 0.5f * NL_SKIN;
-    const bool rb = force || d2 > half * half;
-    if (b == 0 && lane == 0) rebuild[r] = rb;
-    if (!rb) return;
-    const int i = b * 64 + lane;
-    xref[rd.poff + i] = xs[2 * rd.poff + b * 128 + lane];
+    for (int o = 32; o > 0; o >>= 1) d2 = fmax(d2, __shfl_xor(d2, o, 64));
+    if (lane == 0) bounds[(int64_t)r * nb_max + b] = make_float4((float)cx, (float)cy, (float)cz, (float)sqrt(d2));
+    xref[rd.poff + i] = p;
     cnt[rd.poff + i] = 0;
 }
 
@@ -2234,11 +2221,12 @@ __global__ __launch_bounds__(256) void k_nl_force(const KParams P, const SysDesc
                                                   const RepDesc *__restrict__ reps, const int *__restrict__ first,
                                                   const float4 *__restrict__ xs, const int *__restrict__ cnt,
                                                   const int2 *__restrict__ nl, double *__restrict__ acc,
-                                                  double *__restrict__ zpart) {
+                                                  double *__restrict__ zpart, int *__restrict__ rebuild) {
     __shared__ double zw[4];
     const int chunk = blockIdx.x, r = blockIdx.y;
     const RepDesc rd = reps[r];
     const SysDesc S = sysd[rd.sys];
+    if (chunk == 0 && threadIdx.x == 0) rebuild[r] = 0;   // built by now; the update may ask again
     if (chunk * NL_CHUNK >= S.n_pad) return;
     const int tid = threadIdx.x, t = tid % NL_LANES;
     const int i = chunk * NL_CHUNK + tid / NL_LANES;
@@ -2325,14 +2313,18 @@ __global__ __launch_bounds__(256) void k_nl_force(const KParams P, const SysDesc
     if (tid == 0) zpart[first[r] + chunk] = (zw[0] + zw[1]) + (zw[2] + zw[3]);
 }
 
+hipError_t launch_nl_check(const SysDesc *sysd, const RepDesc *reps, int R, int n_pad_max, const float4 *xs,
+                           const float4 *xref, int *rebuild, hipStream_t st) {
+    hipLaunchKernelGGL(k_nl_check, dim3((n_pad_max + 255) / 256, R), dim3(256), 0, st, sysd, reps, xs, xref, rebuild);
+    return hipGetLastError();
+}
+
 hipError_t launch_nl_update(const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R, int nb_max,
-                            const int *first_blk, const float4 *xs, float4 *bounds, float4 *xref, float *bmax,
-                            int *rebuild, int force, const TileItem *items_all, const int *first_all, float r_list,
-                            int *cnt, int2 *nl, int *flags, hipStream_t st) {
-    const dim3 blocks(nb_max, R);
-    hipLaunchKernelGGL(k_nl_blocks, blocks, dim3(64), 0, st, sysd, reps, nb_max, first_blk, xs, xref, bounds, bmax);
-    hipLaunchKernelGGL(k_nl_reset, blocks, dim3(64), 0, st, sysd, reps, first_blk, xs, xref, bmax, force, rebuild,
-                       cnt);
+                            const float4 *xs, float4 *bounds, float4 *xref, int *rebuild, int force,
+                            const TileItem *items_all, const int *first_all, float r_list, int *cnt, int2 *nl,
+                            int *flags, hipStream_t st) {
+    hipLaunchKernelGGL(k_nl_reset, dim3(nb_max, R), dim3(64), 0, st, sysd, reps, nb_max, xs, xref, bounds, force,
+                       rebuild, cnt);
     hipLaunchKernelGGL(k_nl_build, dim3(NL_BUILD_WG), dim3(256), 0, st, P, sysd, reps, R, items_all, first_all, xs,
                        bounds, nb_max, r_list, rebuild, cnt, nl, flags);
     return hipGetLastError();
@@ -2342,11 +2334,11 @@ int nl_chunks(int n_pad) { return (n_pad + NL_CHUNK - 1) / NL_CHUNK; }
 
 hipError_t launch_nl_force(int nbk, const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R,
                            int n_pad_max, const int *first_chunk, const float4 *xs, const int *cnt, const int2 *nl,
-                           double *acc, double *zpart, hipStream_t st) {
+                           double *acc, double *zpart, int *rebuild, hipStream_t st) {
     const dim3 blocks(nl_chunks(n_pad_max), R);
 #define SCPS_NL(K)                                                                                      \
     hipLaunchKernelGGL(k_nl_force<K>, blocks, dim3(256), 0, st, P, sysd, reps, first_chunk, xs, cnt, nl, acc, \
-                       zpart)
+                       zpart, rebuild)
     switch (nbk) {
     case 0: SCPS_NL(0); break;
     case 1: SCPS_NL(1); break;
@@ -2436,7 +2428,8 @@ __global__ __launch_bounds__(256) void k_integrate(const KParams P, const SysDes
                                                    const double *__restrict__ scale, double *__restrict__ cv,
                                                    const uint64_t step_off, const uint64_t *__restrict__ step_base,
                                                    int *__restrict__ flags, const int *__restrict__ zfirst,
-                                                   const double *__restrict__ zpart, const double *__restrict__ zbase) {
+                                                   const double *__restrict__ zpart, const double *__restrict__ zbase,
+                                                   const float4 *__restrict__ xref, int *__restrict__ rebuild) {
     __shared__ double tred[4];
     __shared__ double sh_scale;
     const uint64_t step = step_off + (step_base ? *step_base : 0u);
@@ -2492,6 +2485,7 @@ __global__ __launch_bounds__(256) void k_integrate(const KParams P, const SysDes
         langevin_update(P, inv_m, F, (uint32_t)S.perm[a], P.rep_base + (uint32_t)r, step, np, q);
         if (P.integrator != 0) vs[rd.poff + a] = q;
         if (!(isfinite(np.x) && isfinite(np.y) && isfinite(np.z))) flags[r] = 1;
+        if (rebuild && nl_moved(np, xref[rd.poff + a])) rebuild[r] = 1;   // neighbour lists
         xr2[da] = np;
         xr2[da + 64] = np;
     }
@@ -2507,9 +2501,9 @@ __global__ __launch_bounds__(256) void k_integrate(const KParams P, const SysDes
 hipError_t launch_integrate(const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R, int n_pad_max,
                             float4 *xs, float4 *vs, double *acc, const double *scale, double *cv, uint64_t step,
                             const uint64_t *step_base, int *flags, hipStream_t st, const int *zfirst,
-                            const double *zpart, const double *zbase) {
+                            const double *zpart, const double *zbase, const float4 *xref, int *rebuild) {
     hipLaunchKernelGGL(k_integrate, dim3((n_pad_max + 255) / 256, R), dim3(256), 0, st, P, sysd, reps, xs, vs, acc,
-                       scale, cv, step, step_base, flags, zfirst, zpart, zbase);
+                       scale, cv, step, step_base, flags, zfirst, zpart, zbase, xref, rebuild);
     return hipGetLastError();
 }
 
