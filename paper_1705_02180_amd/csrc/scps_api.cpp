@@ -271,6 +271,14 @@ int pick_wg(int nb, int n_replicas) {
     return n_replicas < 512 ? 256 : 64;
 }
 
+// What the split launch asks before it looks at the short segments. Only contexts
+// that pass make them: built for every system they took preparing 64 chains of 3000
+// particles from 65 to 79 ms in the worst of four runs (67 both ways now).
+bool may_split(const scps_ctx *c, const scps_params &p) {
+    return p.bias_mode == SCPS_BIAS_RMD && p.exec_mode == SCPS_EXEC_AUTO && c->wg == 1024 && c->R <= 128 &&
+           split_lds_bytes(c->n_pad_max) <= 160 * 1024;
+}
+
 // Workgroups per replica of the 1024-thread launch: 1 (the persistent kernel,
 // one launch a call) or G > 1 (the split kernel, one launch a step), as many as
 // find a CU of their own and at least 4 short segments of the longest chain.
@@ -281,7 +289,6 @@ int pick_wg(int nb, int n_replicas) {
 // against 11.2 split at 120 particles x 32, 18.8 against 13.1 at 200 x 64, 47.7
 // against 40 at 560 x 128 (G = 2).
 int pick_split(const scps_ctx *c) {
-    if (c->wg != 1024 || split_lds_bytes(c->n_pad_max) > 160 * 1024) return 1;
     double cost = 0.0;
     size_t items = 0;
     for (int s : c->rep_sys) {
@@ -419,7 +426,6 @@ void build_list(const SysHost &h, const int seg, const int seg2, const int tail_
 
 void build_schedule(SysHost &h) {
     build_list(h, SEG_STEPS, SEG_STEPS, TAIL_ITEMS, h.sched, h.sched_mask, &h.sched_cost);
-    build_list(h, FINE_STEPS, FINE_STEPS / 2, 0, h.sched_f, h.sched_f_mask, nullptr);
 }
 
 // Replicas of each system in groups of up to SCPS_GROUP, one item per
@@ -570,6 +576,11 @@ scps_status init_impl(const scps_params *params, const scps_topology *topo, int3
         compute_tile_flags(h, p);
         build_schedule(h);
     }
+    if (may_split(c, p)) {
+        for (auto &h : c->sys)
+            build_list(h, FINE_STEPS, FINE_STEPS / 2, 0, h.sched_f, h.sched_f_mask, nullptr);
+        c->split_G = pick_split(c);
+    }
 
     // device buffers
     for (auto &h : c->sys) {
@@ -586,6 +597,7 @@ scps_status init_impl(const scps_params *params, const scps_topology *topo, int3
         HIP_TRY(c, dalloc(c, &h.d_sched_mask, h.sched_mask.size()));
         HIP_TRY(c, hipMemcpy(h.d_sched_mask, h.sched_mask.data(), h.sched_mask.size() * sizeof(uint64_t),
                              hipMemcpyHostToDevice));
+        if (c->split_G == 1) continue;   // only the split launch reads the short segments
         HIP_TRY(c, dalloc(c, &h.d_sched_f, h.sched_f.size()));
         HIP_TRY(c, hipMemcpy(h.d_sched_f, h.sched_f.data(), h.sched_f.size() * sizeof(int2), hipMemcpyHostToDevice));
         HIP_TRY(c, dalloc(c, &h.d_sched_f_mask, h.sched_f_mask.size()));
@@ -670,7 +682,6 @@ scps_status init_impl(const scps_params *params, const scps_topology *topo, int3
         HIP_TRY(c, dalloc(c, &c->d_zbase, R));
         HIP_TRY(c, hipMemset(c->d_zbase, 0, R * sizeof(double)));
     }
-    if (p.bias_mode == SCPS_BIAS_RMD && p.exec_mode == SCPS_EXEC_AUTO) c->split_G = pick_split(c);
     if (c->split_G > 1) {
         for (int k = 0; k < 2; ++k) {
             HIP_TRY(c, dalloc(c, &c->split.xs[k], c->sumNpad));
