@@ -78,7 +78,7 @@ __constant__ const double2 EXP2_64[64] = {
 // to hi last, so the result carries little more than one rounding (largest error
 // 0.51 units in the last place over 4e6 random arguments).  14 float64
 // instructions, where exp took 21 and three selects for the ranges that do not
-// occur here.  Arguments below -746 give 0.
+// occur here.  Arguments below -746 give 0; so does NaN, which the caller looks for.
 __device__ __forceinline__ double exp_neg(double x, const double2 *tab) {
     x = fmax(x, -746.0);
     const double magic = 0x1.8p52;
@@ -154,12 +154,18 @@ __global__ __launch_bounds__(256) void k_funnel_steps(const FunnelK P, int n_tra
     __shared__ double2 path[FUNNEL_KMAX];
     __shared__ double2 tab[64];
     __shared__ __align__(16) FunnelChunk chunk[L > 1 ? 256 / L : 1];
+    bool path_nan = false;
     if (BIAS == 1) {
         if (L > 1 && threadIdx.x / L < 256 / L)
             for (int q = threadIdx.x % L; q < FCH; q += L) chunk[threadIdx.x / L].col[4][q] = 1.0;
-        for (int k = threadIdx.x; k < K; k += blockDim.x) path[k] = mp[k];
+        bool nan = false;
+        for (int k = threadIdx.x; k < K; k += blockDim.x) {
+            const double2 f = mp[k];
+            path[k] = f;
+            nan |= f.x != f.x || f.y != f.y;
+        }
         if (threadIdx.x < 64) tab[threadIdx.x] = EXP2_64[threadIdx.x];
-        __syncthreads();
+        path_nan = __syncthreads_or(nan);
     }
     const int thread = blockIdx.x * blockDim.x + threadIdx.x;
     const int sub = thread % L;
@@ -267,7 +273,9 @@ __global__ __launch_bounds__(256) void k_funnel_steps(const FunnelK P, int n_tra
             ay *= 2.0;
             kx *= 2.0;
             ky *= 2.0;
-            if (!(d_min < INFINITY)) s0 = NAN;   // a position that is not finite has no weights
+            // no weights where exp_neg would hide it: a position that is not finite (or so far
+            // that the exponent overflows), a path with a frame that is not a number
+            if (!(a > -INFINITY) || path_nan) s0 = NAN;
             const double kbar = s1 / s0;
             sv = 1.0 - kbar / M;
             wv = tube_w(a, s0, P.wscale);
