@@ -310,15 +310,31 @@ __global__ __launch_bounds__(256) void k_funnel_steps(const FunnelK P, int n_tra
     c[CV_T] = T;
 }
 
+// Lanes per trajectory under the tube ratchets: as long as the lanes give a SIMD
+// (256 CUs x 4) no more than one or two wavefronts, and the mean path is long
+// enough for the exchange through LDS, which costs a chunk of FCH frames however
+// few there are.  us for 50 steps with 1 / 8 / 16 lanes:
+//   frames        4096 trajectories    8192                 16384
+//     2              75 /  90 /  87      74 /  93 / 132       75 / 137 / 236
+//     5              88 /  90 /  87      87 /  92 / 132       87 / 135 / 236
+//     7             101 /  90 /  87      99 /  92 / 132       99 / 134 / 236
+//     9             108 /  97 /  87     107 / 100 / 132      106 / 144 / 236
+//    20             161 / 119 / 105     159 / 119 / 156      159 / 174 / 272
+//    24             180 / 119 / 105     178 / 120 / 156      178 / 174 / 272
+//    51             317 / 169 / 143     319 / 170 / 204      317 / 242 / 361
+//   128             688 / 274 / 203     690 / 275 / 292      691 / 391 / 527
+// Above 16384 a lane each (51 frames, 20000 trajectories: 319 / 322 / 434).
+static int funnel_lanes(int n_traj, int K) {
+    if (n_traj <= 4096 && K >= 5) return 16;
+    if (n_traj <= 8192 && K >= 7) return 8;
+    if (n_traj <= 16384 && K >= 24) return 8;
+    return 1;
+}
+
 hipError_t launch_funnel_steps(const FunnelK &P, int n_traj, int first_id, double2 *xy, double *cv, int64_t n_steps,
                                uint64_t step0, int record_every, double2 *frames, int K, const double2 *mp,
                                hipStream_t st) {
-    // lanes per trajectory under the tube ratchets: as long as the lanes give a
-    // SIMD (256 CUs x 4) no more than one or two wavefronts.  16, 8, 4 and 1 lanes
-    // took 145, 168, 243 and 315 us at 4096 trajectories, 362, 241, 244 and 318 at
-    // 16384, 434, 322, 357 and 319 at 20000.
-    int lanes = 1;
-    if (P.bias_mode == 1) lanes = n_traj <= 4096 ? 16 : n_traj <= 16384 ? 8 : 1;
+    const int lanes = P.bias_mode == 1 ? funnel_lanes(n_traj, K) : 1;
     const dim3 grid((unsigned)(((int64_t)n_traj * lanes + 255) / 256)), block(256);
 #define SCPS_FUNNEL(BIAS, L)                                                                                   \
     hipLaunchKernelGGL((k_funnel_steps<BIAS, L>), grid, block, 0, st, P, n_traj, first_id, xy, cv, n_steps, step0, \
