@@ -121,6 +121,7 @@ struct scps_ctx {
     ScpsItem *d_sitems = nullptr;
     int n_sitems = 0;
     int max_group = 0;            // replicas of the largest group
+    int xq_sets = 1;              // sets of the distance pass's sums X, Q
     int kmax = KMAX;
     int wg = 64;     // persistent workgroup size
     int split_G = 1;          // workgroups per replica of the 1024-thread launch (> 1: one launch per step)
@@ -435,17 +436,9 @@ void build_schedule(SysHost &h) {
 scps_status ensure_scps_groups(scps_ctx *c) {
     if (c->d_groups) return SCPS_OK;
     const int R = c->R;
-    const size_t xq = (size_t)R * XQ_COPIES;
-    HIP_TRY(c, dalloc(c, &c->d_X, xq * c->kmax));
-    HIP_TRY(c, hipMemset(c->d_X, 0, xq * c->kmax * sizeof(double)));
-    HIP_TRY(c, dalloc(c, &c->d_Q, xq));
-    HIP_TRY(c, hipMemset(c->d_Q, 0, xq * sizeof(double)));
-    HIP_TRY(c, dalloc(c, &c->d_jref, R));
-    HIP_TRY(c, hipMemset(c->d_jref, 0, R * sizeof(int)));
-    HIP_TRY(c, dalloc(c, &c->d_jref_eval, R));
-    c->jref_init = true;
     std::vector<ScpsGroup> groups;
     std::vector<ScpsItem> items;
+    int most_items = 0;   // of a group
     for (int s = 0; s < (int)c->sys.size(); ++s) {
         std::vector<int> mine;
         for (int r = 0; r < R; ++r)
@@ -459,6 +452,7 @@ scps_status ensure_scps_groups(scps_ctx *c) {
             for (int k = 0; k < g.nrep; ++k) g.rep[k] = mine[b + k];
             const int gi = (int)groups.size();
             groups.push_back(g);
+            most_items = std::max(most_items, h.ntile_c);
             // diagonal by diagonal (J - I = d), so that the items that run at the
             // same time add their forces to different blocks
             for (int d = 0; d < h.ncb; ++d)
@@ -470,6 +464,17 @@ scps_status ensure_scps_groups(scps_ctx *c) {
         }
     }
     c->n_sitems = (int)items.size();
+    // the workgroups of the distance pass that can meet on one group's sums
+    c->xq_sets = (int64_t)most_items * scps_dist_splits(c->n_sitems) > XQ_MEET ? XQ_SETS : 1;
+    const size_t xq = (size_t)R * c->xq_sets;
+    HIP_TRY(c, dalloc(c, &c->d_X, xq * c->kmax));
+    HIP_TRY(c, hipMemset(c->d_X, 0, xq * c->kmax * sizeof(double)));
+    HIP_TRY(c, dalloc(c, &c->d_Q, xq));
+    HIP_TRY(c, hipMemset(c->d_Q, 0, xq * sizeof(double)));
+    HIP_TRY(c, dalloc(c, &c->d_jref, R));
+    HIP_TRY(c, hipMemset(c->d_jref, 0, R * sizeof(int)));
+    HIP_TRY(c, dalloc(c, &c->d_jref_eval, R));
+    c->jref_init = true;
     HIP_TRY(c, dalloc(c, &c->d_groups, groups.size()));
     HIP_TRY(c, hipMemcpy(c->d_groups, groups.data(), groups.size() * sizeof(ScpsGroup), hipMemcpyHostToDevice));
     HIP_TRY(c, dalloc(c, &c->d_sitems, items.size()));
@@ -911,10 +916,11 @@ scps_status step_launches(scps_ctx *c, double *cv, uint64_t step, const uint64_t
     }
     if (tev) HIP_TRY(c, hipEventRecord(tev[0], st));
     HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems,
-                                max_stack_frames(c), c->max_group, c->d_jref, c->d_xs, c->d_X, c->d_Q, c->kmax, -1, st));
+                                max_stack_frames(c), c->max_group, c->d_jref, c->d_xs, c->d_X, c->d_Q, c->xq_sets,
+                                c->kmax, -1, st));
     if (tev) HIP_TRY(c, hipEventRecord(tev[1], st));
-    HIP_TRY(c, launch_finalize_scps(c->kp, c->d_sysd, c->d_reps, c->R, c->kmax, c->d_jref, c->d_X, c->d_Q, cv,
-                                    c->d_coef, c->d_csum, st));
+    HIP_TRY(c, launch_finalize_scps(c->kp, c->d_sysd, c->d_reps, c->R, c->kmax, c->d_jref, c->d_X, c->d_Q,
+                                    c->xq_sets, cv, c->d_coef, c->d_csum, st));
     if (tev) HIP_TRY(c, hipEventRecord(tev[2], st));
     if (c->prm.exec_mode == SCPS_EXEC_PER_STEP_ALL_TILES) {
         // two passes: effective references to device memory, then every tile pair
@@ -1031,10 +1037,10 @@ scps_status step_impl(scps_ctx *c, float *x, float *v, double *cv, int64_t n_ste
             // a new stack: every replica's reference frame is its nearest frame,
             // from one distance pass around frame 0
             HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems,
-                                        max_stack_frames(c), c->max_group, nullptr, c->d_xs, c->d_X, c->d_Q, c->kmax, -1,
-                                        c->stream));
+                                        max_stack_frames(c), c->max_group, nullptr, c->d_xs, c->d_X, c->d_Q,
+                                        c->xq_sets, c->kmax, -1, c->stream));
             HIP_TRY(c, launch_tube_eval(c->prm.lambda, c->kp.wscale, nullptr, c->d_jref, c->d_sysd, c->d_reps,
-                                        c->R, c->kmax, -1, c->d_X, c->d_Q, nullptr, nullptr, nullptr, 0.0, 1,
+                                        c->R, c->kmax, -1, c->d_X, c->d_Q, c->xq_sets, nullptr, nullptr, nullptr, 0.0, 1,
                                         c->stream));
             c->jref_init = false;
         }
@@ -1182,15 +1188,17 @@ scps_status eval_tube_impl(scps_ctx *c, int32_t n_stacks, const int32_t *stacks,
     for (int k = 0; k < n_stacks; ++k) {
         // two passes: around frame 0, to find each replica's nearest frame, then around that frame
         const int K = c->sys[stacks[k]].K;
-        HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems, K, c->max_group, nullptr,
-                                    c->d_xs, c->d_X, c->d_Q, c->kmax, stacks[k], c->stream));
+        HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems, K,
+                                    c->max_group, nullptr, c->d_xs, c->d_X, c->d_Q, c->xq_sets, c->kmax, stacks[k],
+                                    c->stream));
         HIP_TRY(c, launch_tube_eval(c->prm.lambda, c->kp.wscale, nullptr, c->d_jref_eval, c->d_sysd, c->d_reps, c->R,
-                                    c->kmax, stacks[k], c->d_X, c->d_Q, nullptr, nullptr, nullptr, 0.0, 1,
+                                    c->kmax, stacks[k], c->d_X, c->d_Q, c->xq_sets, nullptr, nullptr, nullptr, 0.0, 1,
                                     c->stream));
         HIP_TRY(c, launch_scps_dist(c->kp, c->d_sysd, c->d_reps, c->d_groups, c->d_sitems, c->n_sitems, K,
-                                    c->max_group, c->d_jref_eval, c->d_xs, c->d_X, c->d_Q, c->kmax, stacks[k], c->stream));
+                                    c->max_group, c->d_jref_eval, c->d_xs, c->d_X, c->d_Q, c->xq_sets, c->kmax,
+                                    stacks[k], c->stream));
         HIP_TRY(c, launch_tube_eval(c->prm.lambda, c->kp.wscale, c->d_jref_eval, nullptr, c->d_sysd, c->d_reps, c->R,
-                                    c->kmax, stacks[k], c->d_X, c->d_Q, s, w, sigma, 1.0 / n_stacks, k == 0,
+                                    c->kmax, stacks[k], c->d_X, c->d_Q, c->xq_sets, s, w, sigma, 1.0 / n_stacks, k == 0,
                                     c->stream));
     }
     return SCPS_OK;

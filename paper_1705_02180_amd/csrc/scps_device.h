@@ -65,29 +65,28 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// The distance pass adds into XQ_COPIES sets of sums X[r][copy][kmax], Q[r][copy]
-// (workgroup b into set b mod XQ_COPIES): atomics on one address wait for each
-// other, and in a small system all workgroups meet on one group's sums.  Adds
-// the sets up in order (the lane's frames lane, lane + 64 into yk) and clears
-// them; returns sum u^2.
+// The distance pass adds into SETS sets of sums X[r][set][kmax], Q[r][set]
+// (workgroup b into set b mod SETS).  Adds the sets up in order (the lane's frames
+// lane, lane + 64 into yk) and clears them; returns sum u^2.
+template <int SETS>
 __device__ __forceinline__ double take_xq(int lane, int K, int kmax, int r, double *__restrict__ X,
                                           double *__restrict__ Q, double yk[2]) {
-    double *xr = X + (int64_t)r * XQ_COPIES * kmax, *qr = Q + (int64_t)r * XQ_COPIES;
+    double *xr = X + (int64_t)r * SETS * kmax, *qr = Q + (int64_t)r * SETS;
     // one set per lane: vector loads, which a later store of the same wavefront to
     // the same address does not overtake (scalar loads of a uniform address it may)
-    const double q = wave_sum(lane < XQ_COPIES ? qr[lane] : 0.0);
+    const double q = wave_sum(lane < SETS ? qr[lane] : 0.0);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int k = lane + 64 * h;
         yk[h] = 0.0;
         if (k < K) {
 #pragma unroll
-            for (int c = 0; c < XQ_COPIES; ++c) yk[h] += xr[c * kmax + k];
+            for (int c = 0; c < SETS; ++c) yk[h] += xr[c * kmax + k];
 #pragma unroll
-            for (int c = 0; c < XQ_COPIES; ++c) xr[c * kmax + k] = 0.0;
+            for (int c = 0; c < SETS; ++c) xr[c * kmax + k] = 0.0;
         }
     }
-    if (lane < XQ_COPIES) qr[lane] = 0.0;
+    if (lane < SETS) qr[lane] = 0.0;
     return q;
 }
 

@@ -67,7 +67,16 @@ struct RepDesc {
     int64_t eoff;            // SCPS: offset of its effective reference [ntile_c][64*64]
 };
 
-constexpr int XQ_COPIES = 16;   // sets of the distance pass's sums (see take_xq)
+// Sets of the distance pass's sums (see take_xq): 1, or XQ_SETS where more than
+// XQ_MEET workgroups can meet on one group of replicas.  Atomics on one address wait
+// for each other, which shows from about fifty workgroups on; below that more
+// sets only cost the kernel that adds them up.  us a step with 1 / 16 sets, 51
+// frames: 15 tiles x 16 workgroups (32 x 320 particles) 58.4 / 54.7, 96 workgroups
+// (32 x 150) 50.6 / 49.1, 48 (32 x 128) 46.1 / 45.8, 16 (512 x 20) 53.9 / 54.4, 4 (2048 x
+// 60) 91.5 / 95.3, 2 (4096 x 60) 126 / 140; two to eight sets were no better than one.
+constexpr int XQ_SETS = 16, XQ_MEET = 32;
+// Workgroups that take the rows of a tile in the distance pass over n_items items.
+int scps_dist_splits(int n_items);
 
 // SCPS: up to 32 replicas of one system share every read of the frame stack.
 constexpr int SCPS_GROUP = 32;
@@ -184,17 +193,17 @@ hipError_t launch_pairs(int mode, int nbk, const KParams &P, const SysDesc *sysd
 // of the stacks read (1 .. KMAX), max_group the largest number of replicas in a
 // group: the kernel's frame blocks and row groups.
 // jref [R]: each replica's reference frame j of the distance expansion (NULL:
-// frame 0); X [R][XQ_COPIES][kmax] receives Y_k = sum_p (C_p - R_jp) R_kp and
-// Q [R][XQ_COPIES] sum_p (C_p - R_jp)^2, in XQ_COPIES parts.
+// frame 0); X [R][sets][kmax] receives Y_k = sum_p (C_p - R_jp) R_kp and
+// Q [R][sets] sum_p (C_p - R_jp)^2, in `sets` parts.
 hipError_t launch_scps_dist(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
                             const ScpsItem *items, int n_items, int max_frames, int max_group, const int *jref,
-                            const float4 *xs, double *X, double *Q, int kmax, int stack_sys, hipStream_t st);
+                            const float4 *xs, double *X, double *Q, int sets, int kmax, int stack_sys, hipStream_t st);
 // s, w, sigma of every replica from the distances in X, Q (which it clears);
 // jref_in: the reference frames the distance pass used (NULL: frame 0);
 // jref_out (nullable): each replica's frame of largest weight.
 hipError_t launch_tube_eval(double lam, double wscale, const int *jref_in, int *jref_out, const SysDesc *sysd,
-                            const RepDesc *reps, int R, int kmax, int stack_sys, double *X, double *Q, double *s,
-                            double *w, double *sigma, double weight, int first, hipStream_t st);
+                            const RepDesc *reps, int R, int kmax, int stack_sys, double *X, double *Q, int sets,
+                            double *s, double *w, double *sigma, double weight, int first, hipStream_t st);
 hipError_t launch_scps_eff(const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups, const ScpsItem *items,
                            int n_items, const float *coef, int kmax, float *E, hipStream_t st);
 // Effective references and the contact bias forces in one pass (no E in
@@ -240,8 +249,8 @@ hipError_t launch_tile_sumsq(int nc, int ncb, int min_sep, const int *perm, cons
 // jref [R]: read as the distance pass's reference frames, then set to each
 // replica's frame of largest weight for the next step.
 hipError_t launch_finalize_scps(const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R,
-                                int kmax, int *jref, double *X, double *Q, double *cv, float *coef, double *csum,
-                                hipStream_t st);
+                                int kmax, int *jref, double *X, double *Q, int sets, double *cv, float *coef,
+                                double *csum, hipStream_t st);
 // The update of one step.  The contact-gradient accumulators are scaled by
 // scale[r], or, when zpart is not NULL, by the rMD ratchet of eq (FrMD)
 // computed in the same launch (cvstate's z, z_m and E_b written): z of

@@ -2363,6 +2363,7 @@ hipError_t launch_nl_force(int nbk, const KParams &P, const SysDesc *sysd, const
 // coef receives c_k / Z0 and csum sum_k c_k / Z0 for the gradient pass, and
 // jref[r] the frame of largest weight, the reference of the next step's
 // distance pass.  X and Q are consumed and cleared.
+template <int SETS>
 __global__ void k_finalize_scps(const KParams P, const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
                                 const int kmax, int *__restrict__ jref, double *__restrict__ X,
                                 double *__restrict__ Q, double *__restrict__ cv, float *__restrict__ coef,
@@ -2374,7 +2375,7 @@ __global__ void k_finalize_scps(const KParams P, const SysDesc *__restrict__ sys
     const double lam = P.lambda;
     const int j = ref_frame(jref, r, K);
     double yk[2];
-    const double q = take_xq(lane, K, kmax, r, X, Q, yk);
+    const double q = take_xq<SETS>(lane, K, kmax, r, X, Q, yk);
     const TubeSums ts = tube_sums(lane, K, q, yk, j, S.G + (int64_t)j * K, S.Z0, lam);
     const double *e = ts.e;
     const double a = ts.a, s0 = ts.s0, s1 = ts.s1;
@@ -2410,9 +2411,10 @@ __global__ void k_finalize_scps(const KParams P, const SysDesc *__restrict__ sys
 }
 
 hipError_t launch_finalize_scps(const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R, int kmax,
-                                int *jref, double *X, double *Q, double *cv, float *coef, double *csum,
+                                int *jref, double *X, double *Q, int sets, double *cv, float *coef, double *csum,
                                 hipStream_t st) {
-    hipLaunchKernelGGL(k_finalize_scps, dim3(R), dim3(64), 0, st, P, sysd, reps, kmax, jref, X, Q, cv, coef, csum);
+    const auto kernel = sets == 1 ? k_finalize_scps<1> : k_finalize_scps<XQ_SETS>;
+    hipLaunchKernelGGL(kernel, dim3(R), dim3(64), 0, st, P, sysd, reps, kmax, jref, X, Q, cv, coef, csum);
     return hipGetLastError();
 }
 

@@ -809,7 +809,8 @@ __attribute__((amdgpu_waves_per_eu(dist_resident<NR, NB>() * DIST_NW / 4, dist_r
 void k_scps_dist(const KParams P, const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps,
                  const ScpsGroup *__restrict__ groups, const ScpsItem *__restrict__ items, const int n_items,
                  const int nsplit, const int *__restrict__ jref, const float4 *__restrict__ xs,
-                 double *__restrict__ X, double *__restrict__ Q, const int kmax, const int stack_sys) {
+                 double *__restrict__ X, double *__restrict__ Q, const int sets, const int kmax,
+                 const int stack_sys) {
     __shared__ __align__(16) DistLds<NR, NB> L;
     constexpr int WG = 64 * DIST_NW, SLOTS = 16 * NR, COLS = 16 * NB;
     // the wavefront index is uniform: in a scalar register, the row and step
@@ -823,14 +824,14 @@ void k_scps_dist(const KParams P, const SysDesc *__restrict__ sysd, const RepDes
     int cur = -1, nrep = 0;
     SysDesc S;
     const int n_units = n_items * nsplit, rows = 64 / nsplit;
-    const int copy = blockIdx.x % XQ_COPIES;
+    const int set = blockIdx.x & (sets - 1);
     for (int t = blockIdx.x;; t += gridDim.x) {
         const bool more = t < n_units;
         const int u = t / nsplit, r0 = (t - u * nsplit) * rows;
         const ScpsItem it = more ? items[u] : ScpsItem{-1, 0, 0, 0};
         const bool change = it.group != cur;
         if (cur >= 0 && change) {
-            // flush the group's sums to one of the replicas' XQ_COPIES float64 totals
+            // flush the group's sums to one set of the replicas' float64 totals
 #pragma unroll
             for (int g = 0; g < NR; ++g) {
                 unsafeAtomicAdd(&L.qs[16 * g + (lane & 15)], q[g]);
@@ -840,11 +841,11 @@ void k_scps_dist(const KParams P, const SysDesc *__restrict__ sysd, const RepDes
             for (int e = tid; e < SLOTS * COLS; e += WG) {
                 const int slot = e / COLS, c = e % COLS, k = dist_frame<NB>(c >> 4, c & 15);
                 if (slot < nrep && k < S.K)
-                    unsafeAtomicAdd(&X[((int64_t)L.rep[slot] * XQ_COPIES + copy) * kmax + k], L.xl[slot][c]);
+                    unsafeAtomicAdd(&X[((int64_t)L.rep[slot] * sets + set) * kmax + k], L.xl[slot][c]);
                 L.xl[slot][c] = 0.0;
             }
             if (tid < SLOTS) {
-                if (tid < nrep) unsafeAtomicAdd(&Q[L.rep[tid] * XQ_COPIES + copy], L.qs[tid]);
+                if (tid < nrep) unsafeAtomicAdd(&Q[L.rep[tid] * sets + set], L.qs[tid]);
                 L.qs[tid] = 0.0;
             }
         }
@@ -1350,14 +1351,11 @@ __global__ __launch_bounds__(BIAS_WG) __attribute__((amdgpu_waves_per_eu(3, 3)))
     }
 }
 
-template <int NR, int NB>
-static void launch_scps_dist_as(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
-                                const ScpsItem *items, int n_items, const int *jref, const float4 *xs, double *X,
-                                double *Q, int kmax, int stack_sys, hipStream_t st) {
-    // each tile's rows are split over up to 16 workgroups where that shortens the
-    // pass: rounds of 256 CUs, each 8 / ns rows of a wavefront and the staging and
-    // first loads of a unit (about 0.7 rows; 16 ranges leave half the wavefronts
-    // without a row and were still faster than 8 at 15 tiles)
+// Each tile's rows are split over up to 16 workgroups where that shortens the
+// pass: rounds of 256 CUs, each 8 / ns rows of a wavefront and the staging and
+// first loads of a unit (about 0.7 rows; 16 ranges leave half the wavefronts
+// without a row and were still faster than 8 at 15 tiles)
+int scps_dist_splits(int n_items) {
     int ns = 1;
     double best = 1e30;
     for (int k = 1; k <= 16; k *= 2) {
@@ -1367,22 +1365,32 @@ static void launch_scps_dist_as(const KParams &P, const SysDesc *sysd, const Rep
             ns = k;
         }
     }
+    return ns;
+}
+
+template <int NR, int NB>
+static void launch_scps_dist_as(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
+                                const ScpsItem *items, int n_items, const int *jref, const float4 *xs, double *X,
+                                double *Q, int sets, int kmax, int stack_sys, hipStream_t st) {
+    const int ns = scps_dist_splits(n_items);
     const int grid = std::min(n_items * ns, 256 * dist_resident<NR, NB>());
     hipLaunchKernelGGL((k_scps_dist<NR, NB>), dim3(grid), dim3(64 * DIST_NW), 0, st, P, sysd, reps, groups, items,
-                       n_items, ns, jref, xs, X, Q, kmax, stack_sys);
+                       n_items, ns, jref, xs, X, Q, sets, kmax, stack_sys);
 }
 
 hipError_t launch_scps_dist(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
                             const ScpsItem *items, int n_items, int max_frames, int max_group, const int *jref,
-                            const float4 *xs, double *X, double *Q, int kmax, int stack_sys, hipStream_t st) {
+                            const float4 *xs, double *X, double *Q, int sets, int kmax, int stack_sys,
+                            hipStream_t st) {
     if (n_items == 0) return hipSuccess;
+    if (sets != 1 && sets != XQ_SETS) return hipErrorInvalidValue;
     if (max_frames < 1 || max_frames > KMAX || max_frames > kmax) return hipErrorInvalidValue;
 #define SCPS_DIST(NB)                                                                                              \
     do {                                                                                                           \
         if (max_group <= 16)                                                                                       \
-            launch_scps_dist_as<1, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, kmax, stack_sys, st); \
+            launch_scps_dist_as<1, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, sets, kmax, stack_sys, st); \
         else                                                                                                       \
-            launch_scps_dist_as<2, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, kmax, stack_sys, st); \
+            launch_scps_dist_as<2, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, sets, kmax, stack_sys, st); \
     } while (0)
     switch ((max_frames + 15) / 16) {
     case 1: SCPS_DIST(1); break;
@@ -1404,6 +1412,7 @@ hipError_t launch_scps_dist(const KParams &P, const SysDesc *sysd, const RepDesc
 // first, else incremented by it (the mean of 1 - s over several stacks is
 // the progress coordinate sigma); jref_out: nullable [R], each replica's
 // frame of largest weight.
+template <int SETS>
 __global__ void k_tube_eval(double lam, double wscale, const int *__restrict__ jref_in, int *__restrict__ jref_out,
                             const SysDesc *__restrict__ sysd, const RepDesc *__restrict__ reps, int kmax,
                             int stack_sys, double *__restrict__ X, double *__restrict__ Q, double *__restrict__ s,
@@ -1413,7 +1422,7 @@ __global__ void k_tube_eval(double lam, double wscale, const int *__restrict__ j
     const int K = S.K;
     const int j = ref_frame(jref_in, r, K);
     double yk[2];
-    const double q = take_xq(lane, K, kmax, r, X, Q, yk);
+    const double q = take_xq<SETS>(lane, K, kmax, r, X, Q, yk);
     const TubeSums ts = tube_sums(lane, K, q, yk, j, S.G + (int64_t)j * K, S.Z0, lam);
     const double sv = 1.0 - (ts.s1 / ts.s0) / (double)(K - 1);
     const double wv = tube_w(ts.a, ts.s0, wscale);
@@ -1426,10 +1435,11 @@ __global__ void k_tube_eval(double lam, double wscale, const int *__restrict__ j
 }
 
 hipError_t launch_tube_eval(double lam, double wscale, const int *jref_in, int *jref_out, const SysDesc *sysd,
-                            const RepDesc *reps, int R, int kmax, int stack_sys, double *X, double *Q, double *s,
-                            double *w, double *sigma, double weight, int first, hipStream_t st) {
-    hipLaunchKernelGGL(k_tube_eval, dim3(R), dim3(64), 0, st, lam, wscale, jref_in, jref_out, sysd, reps, kmax,
-                       stack_sys, X, Q, s, w, sigma, weight, first);
+                            const RepDesc *reps, int R, int kmax, int stack_sys, double *X, double *Q, int sets,
+                            double *s, double *w, double *sigma, double weight, int first, hipStream_t st) {
+    const auto kernel = sets == 1 ? k_tube_eval<1> : k_tube_eval<XQ_SETS>;
+    hipLaunchKernelGGL(kernel, dim3(R), dim3(64), 0, st, lam, wscale, jref_in, jref_out, sysd, reps, kmax, stack_sys,
+                       X, Q, s, w, sigma, weight, first);
     return hipGetLastError();
 }
 
