@@ -465,7 +465,7 @@ scps_status ensure_scps_groups(scps_ctx *c) {
     }
     c->n_sitems = (int)items.size();
     // the workgroups of the distance pass that can meet on one group's sums
-    c->xq_sets = (int64_t)most_items * scps_dist_splits(c->n_sitems) > XQ_MEET ? XQ_SETS : 1;
+    c->xq_sets = (int64_t)most_items * scps_dist_splits(c->n_sitems, 2) > XQ_MEET ? XQ_SETS : 1;
     const size_t xq = (size_t)R * c->xq_sets;
     HIP_TRY(c, dalloc(c, &c->d_X, xq * c->kmax));
     HIP_TRY(c, hipMemset(c->d_X, 0, xq * c->kmax * sizeof(double)));

@@ -75,8 +75,9 @@ struct RepDesc {
 // (32 x 150) 50.6 / 49.1, 48 (32 x 128) 46.1 / 45.8, 16 (512 x 20) 53.9 / 54.4, 4 (2048 x
 // 60) 91.5 / 95.3, 2 (4096 x 60) 126 / 140; two to eight sets were no better than one.
 constexpr int XQ_SETS = 16, XQ_MEET = 32;
-// Workgroups that take the rows of a tile in the distance pass over n_items items.
-int scps_dist_splits(int n_items);
+// Workgroups that take the rows of a tile in the distance pass over n_items items, a
+// CU holding `resident` workgroups (at most 2) at a time.
+int scps_dist_splits(int n_items, int resident);
 
 // SCPS: up to 32 replicas of one system share every read of the frame stack.
 constexpr int SCPS_GROUP = 32;

@@ -841,7 +841,7 @@ void k_scps_dist(const KParams P, const SysDesc *__restrict__ sysd, const RepDes
             for (int e = tid; e < SLOTS * COLS; e += WG) {
                 const int slot = e / COLS, c = e % COLS, k = dist_frame<NB>(c >> 4, c & 15);
                 if (slot < nrep && k < S.K)
-                    unsafeAtomicAdd(&X[((int64_t)L.rep[slot] * sets + set) * kmax + k], L.xl[slot][c]);
+                    unsafeAtomicAdd(&X[(int64_t)(L.rep[slot] * sets + set) * kmax + k], L.xl[slot][c]);
                 L.xl[slot][c] = 0.0;
             }
             if (tid < SLOTS) {
@@ -1352,14 +1352,21 @@ __global__ __launch_bounds__(BIAS_WG) __attribute__((amdgpu_waves_per_eu(3, 3)))
 }
 
 // Each tile's rows are split over up to 16 workgroups where that shortens the
-// pass: rounds of 256 CUs, each 8 / ns rows of a wavefront and the staging and
-// first loads of a unit (about 0.7 rows; 16 ranges leave half the wavefronts
-// without a row and were still faster than 8 at 15 tiles)
-int scps_dist_splits(int n_items) {
+// pass: the CU with the most units takes them one after the other, each 8 / k
+// rows of a wavefront and the staging and first loads of a unit (about 0.7 rows);
+// where it holds two at a time (all but stacks of more than 96 frames with more
+// than 16 replicas) the two together take 0.8 of that.  16 ranges leave half the
+// wavefronts without a row and are still the best at 15 tiles.  us a step for 1 / 2 /
+// 4 / 8 / 16 workgroups a tile, 51 frames (32 x 560: 45 tiles, and so on):
+//   45 tiles   132 /  99 /  84 /  82 /  88      136 tiles  186 / 173 / 162 / 159 / 166
+//   66         153 / 120 / 116 / 114 / 118      240        200 / 192 / 197 / 206 / 227
+//   120        158 / 127 / 122 / 124 / 135      300        298 / 272 / 257 / 268 / 287
+int scps_dist_splits(int n_items, int resident) {
     int ns = 1;
     double best = 1e30;
     for (int k = 1; k <= 16; k *= 2) {
-        const double t = std::ceil(n_items * (double)k / 256.0) * (8.0 / k + 0.7);
+        const double units = std::ceil(n_items * (double)k / 256.0);   // of the fullest CU
+        const double t = units * (8.0 / k + 0.7) * (units > 1.0 && resident > 1 ? 0.8 : 1.0);
         if (t < 0.97 * best) {
             best = t;
             ns = k;
@@ -1372,7 +1379,7 @@ template <int NR, int NB>
 static void launch_scps_dist_as(const KParams &P, const SysDesc *sysd, const RepDesc *reps, const ScpsGroup *groups,
                                 const ScpsItem *items, int n_items, const int *jref, const float4 *xs, double *X,
                                 double *Q, int sets, int kmax, int stack_sys, hipStream_t st) {
-    const int ns = scps_dist_splits(n_items);
+    const int ns = scps_dist_splits(n_items, dist_resident<NR, NB>());
     const int grid = std::min(n_items * ns, 256 * dist_resident<NR, NB>());
     hipLaunchKernelGGL((k_scps_dist<NR, NB>), dim3(grid), dim3(64 * DIST_NW), 0, st, P, sysd, reps, groups, items,
                        n_items, ns, jref, xs, X, Q, sets, kmax, stack_sys);

@@ -36,10 +36,11 @@ def context(R, bias_mode, N=150):
     return ctx, sy, p, maps, X
 
 
-# 150 particles are 6 tiles: a batch of 4 takes them with 96 workgroups (16 sets), one of 520 with 12
-def test_one_set_and_many_give_the_same_tube_variables():
+# 150 particles are 6 tiles a group: a batch of 4 takes them with 96 workgroups (16 sets); 66, 102 and 198
+# tiles take 8, 4 and 2 workgroups each (16 sets, 1 and 1)
+@pytest.mark.parametrize("R", [352, 520, 1050])
+def test_one_set_and_many_give_the_same_tube_variables(R):
     import torch
-    R = 520
     out = []
     for reps in (4, R):
         ctx, sy, p, maps, X = context(reps, 0)
