@@ -352,9 +352,9 @@ scps_status scps_sync(scps_ctx *ctx, int32_t *bad_replicas, int32_t *n_bad);
  * replica where a replica's state fits in one workgroup's LDS (also 64, one
  * wavefront, for chains of at most 256 particles), the packed persistent
  * kernel for chains of at most 64 particles (floor(64 / n) replicas per
- * wavefront, n the longest chain, and 1, 2, 4 or 8 wavefronts per
- * workgroup), and the
- * per-step path -- for n_steps steps on private device copies of
+ * wavefront, n the longest chain, or one replica per wavefront in the batches
+ * that scps_set_launch names, and 1, 2, 4 or 8 wavefronts per workgroup),
+ * and the per-step path -- for n_steps steps on private device copies of
  * (x, v, cvstate), in three rounds taken in turns after one untimed step
  * each, and keeps the one with the fastest run for the context's later calls
  * (exec_mode AUTO only).  An SCPS context has the per-step path alone; with
@@ -366,9 +366,11 @@ scps_status scps_sync(scps_ctx *ctx, int32_t *bad_replicas, int32_t *n_bad);
  *   n_steps: steps timed per configuration, >= 1.
  *   chosen: nullable host int32[2]; receives {0 persistent / 1 per-step /
  *           2 packed, threads per workgroup of the persistent kernel,
- *           replicas per workgroup of the packed kernel, or for an SCPS
- *           context 1 when the nonbonded pass overlaps the distance pass and
- *           0 when it runs after the bias pass}.
+ *           wavefronts per workgroup times floor(64 / n) of the packed one
+ *           (the replicas a workgroup holds, where they are packed), or for an
+ *           SCPS context 1 when the nonbonded pass overlaps the distance pass
+ *           and 0 when it runs after the bias pass}.  scps_get_launch_shape
+ *           tells the forms of paths 0 and 2 apart.
  * Results of later calls differ from an untuned context's only by the order
  * of float64 additions.  Allocates three scratch buffers for the duration of
  * the call and synchronises the stream.  Errors: INVALID_ARG, OOM, HIP. */
@@ -420,12 +422,26 @@ scps_status scps_set_graph_steps(scps_ctx *ctx, int32_t steps);
 /* Reports the launch configuration the next scps_step_replicas call takes,
  * the untuned defaults above resolved:
  *   launch: host int32[2]; receives {path, parameter} in scps_autotune's
- *           encoding (path 0: threads per workgroup; path 2: replicas per
- *           workgroup; path 1: 1 when an SCPS context overlaps the
- *           nonbonded pass with the distance pass, else 0).  Exec modes
- *           other than AUTO, and SCPS contexts, report path 1.
+ *           encoding (path 0: threads per workgroup; path 2: wavefronts
+ *           per workgroup times floor(64 / n); path 1: 1 when an SCPS context
+ *           overlaps the nonbonded pass with the distance pass, else 0).
+ *           Exec modes other than AUTO, and SCPS contexts, report path 1.
  * Host only.  Errors: INVALID_ARG (NULL ctx or launch), STATE (poisoned). */
 scps_status scps_get_launch(scps_ctx *ctx, int32_t *launch);
+
+/* The kernel behind that launch: paths 0 and 2 have two forms each, chosen by
+ * the batch (see scps_set_launch).
+ *   shape: host int32[3]; receives {SCPS_KERNEL_*, replicas per workgroup,
+ *          workgroups per replica}, the last two 0 on the per-step path.
+ * Host only.  Errors: INVALID_ARG (NULL ctx or shape), STATE (poisoned). */
+enum {
+    SCPS_KERNEL_PER_STEP = 0,   /* path 1: a few launches per step */
+    SCPS_KERNEL_PERSISTENT = 1, /* path 0: a workgroup per replica, one launch per call */
+    SCPS_KERNEL_SPLIT = 2,      /* path 0, 1024 threads: several workgroups per replica, n_steps + 1 launches */
+    SCPS_KERNEL_PACKED = 3,     /* path 2: several replicas per wavefront (one above 32 particles), one launch */
+    SCPS_KERNEL_WAVE = 4        /* path 2: one replica per wavefront, several lanes per particle, one launch */
+};
+scps_status scps_get_launch_shape(scps_ctx *ctx, int32_t *shape);
 
 /* Convergence measure of the iteration (the paper's Frobenius distance
  * between iterations I and J): the recorded frames of each iteration, projected

@@ -872,6 +872,23 @@ int launch_path(const scps_ctx *c) {
     return 0;
 }
 
+// The kernel that launch_path stands for, replicas per workgroup and workgroups per
+// replica (0: the kernels of a step differ).
+struct LaunchShape {
+    int kernel, replicas, workgroups;
+};
+LaunchShape launch_shape(const scps_ctx *c) {
+    switch (launch_path(c)) {
+    case 0:
+        if (c->wg == 1024 && c->split_G > 1) return {SCPS_KERNEL_SPLIT, 1, c->split_G};
+        return {SCPS_KERNEL_PERSISTENT, 1, 1};
+    case 2:
+        if (wide_default(c->n_max, c->R)) return {SCPS_KERNEL_WAVE, c->pk_waves, 1};
+        return {SCPS_KERNEL_PACKED, c->pk_waves * (64 / c->n_max), 1};
+    default: return {SCPS_KERNEL_PER_STEP, 0, 0};
+    }
+}
+
 // {path, parameter} as scps_autotune and scps_get_launch report them.
 void launch_report(const scps_ctx *c, int path, int32_t *out) {
     out[0] = path;
@@ -1003,22 +1020,27 @@ scps_status step_impl(scps_ctx *c, float *x, float *v, double *cv, int64_t n_ste
         if (scps && h.K < 2) return fail(SCPS_ERR_STATE, "SCPS mode needs a frame stack of >= 2 maps");
     }
     const int64_t frame_stride = 3 * c->sumN;
-    const int path = launch_path(c);
-    if (path == 2) {
+    const LaunchShape shape = launch_shape(c);
+    switch (shape.kernel) {
+    case SCPS_KERNEL_WAVE:
+        HIP_TRY(c, launch_wide_rmd(c->pk_waves, c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, c->n_max, x, v, cv, n_steps,
+                                   step0, record_every, frames, frame_stride, c->d_flags, c->stream));
+        return SCPS_OK;
+    case SCPS_KERNEL_PACKED:
         HIP_TRY(c, launch_packed_rmd(c->pk_waves, c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, c->n_max, x, v, cv,
                                      n_steps, step0, record_every, frames, frame_stride, c->d_flags, c->stream));
         return SCPS_OK;
-    }
-    if (path == 0 && c->wg == 1024 && c->split_G > 1) {
-        HIP_TRY(c, launch_split_rmd(c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, c->split_G, c->n_pad_max, c->split, x, v,
-                                    cv, n_steps, step0, record_every, frames, frame_stride, c->d_flags, c->stream));
+    case SCPS_KERNEL_SPLIT:
+        HIP_TRY(c, launch_split_rmd(c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, shape.workgroups, c->n_pad_max,
+                                    c->split, x, v, cv, n_steps, step0, record_every, frames, frame_stride,
+                                    c->d_flags, c->stream));
         return SCPS_OK;
-    }
-    if (path == 0) {
-        HIP_TRY(c, launch_persistent_rmd(c->wg, c->nbk, c->kp, c->d_sysd, c->d_reps, c->d_order, c->R, c->n_pad_max, x, v, cv,
-                                         n_steps, step0, record_every, frames, frame_stride, c->d_flags,
+    case SCPS_KERNEL_PERSISTENT:
+        HIP_TRY(c, launch_persistent_rmd(c->wg, c->nbk, c->kp, c->d_sysd, c->d_reps, c->d_order, c->R, c->n_pad_max, x,
+                                         v, cv, n_steps, step0, record_every, frames, frame_stride, c->d_flags,
                                          c->stream));
         return SCPS_OK;
+    default: break;   // per step
     }
     HIP_TRY(c, launch_gather(c->d_sysd, c->d_reps, c->R, c->n_pad_max, x, v, c->d_xs, v ? c->d_vs : nullptr,
                              c->stream));
@@ -1455,6 +1477,17 @@ scps_status scps_get_launch(scps_ctx *ctx, int32_t *launch) {
     if (!usable(ctx, &st)) return st;
     if (!launch) return fail(SCPS_ERR_INVALID_ARG, "launch must not be NULL");
     launch_report(ctx, launch_path(ctx), launch);
+    return SCPS_OK;
+}
+
+scps_status scps_get_launch_shape(scps_ctx *ctx, int32_t *shape) {
+    scps_status st;
+    if (!usable(ctx, &st)) return st;
+    if (!shape) return fail(SCPS_ERR_INVALID_ARG, "shape must not be NULL");
+    const LaunchShape s = launch_shape(ctx);
+    shape[0] = s.kernel;
+    shape[1] = s.replicas;
+    shape[2] = s.workgroups;
     return SCPS_OK;
 }
 

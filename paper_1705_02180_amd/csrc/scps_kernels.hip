@@ -1690,7 +1690,7 @@ __global__ __launch_bounds__(512) void k_rmd_wide(const KParams P, const SysDesc
 // most two.  us for 50 steps, packed / wide: n = 5 82 / 95 (1024 replicas), 10:
 // 112 / 94 (2048), 20: 160 / 112 (2048), 32: 220 / 150 (2048), 45: 1135 / 1157
 // (9000), 48: 345 / 317 (2048), 62: 905 / 911 (5000).
-static bool use_wide(int n_max, int R) { return n_max >= 8 && R <= 2048; }
+bool wide_default(int n_max, int n_replicas) { return n_max >= 8 && n_replicas <= 2048; }
 
 int packed_width_ok(int n_max) { return n_max >= 2 && n_max <= PACK_WMAX; }
 // Without tuning: chains of up to 48 particles (one replica per wavefront at
@@ -1700,25 +1700,29 @@ int packed_default(int n_max, int n_replicas) {
     return packed_width_ok(n_max) && (4 * n_max <= 3 * PACK_WMAX || n_replicas >= 2048);
 }
 
+hipError_t launch_wide_rmd(int waves, int nbk, const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R,
+                           int n_max, float *x, float *v, double *cv, int64_t n_steps, uint64_t step0,
+                           int record_every, float *frames, int64_t frame_stride, int *flags, hipStream_t st) {
+    if (!packed_width_ok(n_max) || waves < 1 || waves > 8) return hipErrorInvalidValue;
+    const dim3 grid((R + waves - 1) / waves), block(64 * waves);
+    const size_t lds = (size_t)waves * WIDE_WAVE_LDS;
+#define SCPS_LAUNCH(K)                                                                                          \
+    hipLaunchKernelGGL((k_rmd_wide<K>), grid, block, lds, st, P, sysd, reps, R, x, v, cv, n_steps, step0,       \
+                       record_every, frames, frame_stride, flags)
+    switch (nbk) {
+    case 0: SCPS_LAUNCH(0); break;
+    case 1: SCPS_LAUNCH(1); break;
+    case 2: SCPS_LAUNCH(2); break;
+    default: SCPS_LAUNCH(3); break;
+    }
+#undef SCPS_LAUNCH
+    return hipGetLastError();
+}
+
 hipError_t launch_packed_rmd(int waves, int nbk, const KParams &P, const SysDesc *sysd, const RepDesc *reps, int R,
                              int n_max, float *x, float *v, double *cv, int64_t n_steps, uint64_t step0,
                              int record_every, float *frames, int64_t frame_stride, int *flags, hipStream_t st) {
     if (!packed_width_ok(n_max) || waves < 1 || waves > 8) return hipErrorInvalidValue;
-    if (use_wide(n_max, R)) {
-        const dim3 wide_grid((R + waves - 1) / waves), wide_block(64 * waves);
-        const size_t wide_lds = (size_t)waves * WIDE_WAVE_LDS;
-#define SCPS_LAUNCH(K)                                                                                             \
-    hipLaunchKernelGGL((k_rmd_wide<K>), wide_grid, wide_block, wide_lds, st, P, sysd, reps, R, x, v, cv, n_steps, step0, \
-                       record_every, frames, frame_stride, flags)
-        switch (nbk) {
-        case 0: SCPS_LAUNCH(0); break;
-        case 1: SCPS_LAUNCH(1); break;
-        case 2: SCPS_LAUNCH(2); break;
-        default: SCPS_LAUNCH(3); break;
-        }
-#undef SCPS_LAUNCH
-        return hipGetLastError();
-    }
     const int W = n_max, per_wg = waves * (64 / W);
     const int grid = (R + per_wg - 1) / per_wg;
     const size_t lds = (size_t)waves * packed_wave_lds_bytes(W);

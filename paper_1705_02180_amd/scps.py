@@ -81,6 +81,8 @@ _lib.scps_set_launch.restype = C.c_int
 _lib.scps_set_launch.argtypes = [_vp, _i32, _i32]
 _lib.scps_get_launch.restype = C.c_int
 _lib.scps_get_launch.argtypes = [_vp, _vp]
+_lib.scps_get_launch_shape.restype = C.c_int
+_lib.scps_get_launch_shape.argtypes = [_vp, _vp]
 _lib.scps_set_graph_steps.restype = C.c_int
 _lib.scps_set_graph_steps.argtypes = [_vp, _i32]
 _lib.scps_least_biased_path.restype = C.c_int
@@ -112,9 +114,11 @@ _lib.scps_destroy.argtypes = [_vp]
 _lib.scps_last_error.restype = C.c_char_p
 _lib.scps_last_error.argtypes = []
 
+KERNELS = ("per step", "persistent", "split", "packed", "wave")
+
 EXPORTS = ["scps_init_system", "scps_set_reference_map", "scps_step_replicas", "scps_eval_z_and_grad",
            "scps_ratchet_energy", "scps_update_reference_from_paths", "scps_set_stream", "scps_sync",
-           "scps_autotune", "scps_set_launch", "scps_get_launch", "scps_set_graph_steps", "scps_least_biased_path", "scps_eval_tube", "scps_eval_sigma", "scps_path_distance",
+           "scps_autotune", "scps_set_launch", "scps_get_launch", "scps_get_launch_shape", "scps_set_graph_steps", "scps_least_biased_path", "scps_eval_tube", "scps_eval_sigma", "scps_path_distance",
            "scps_path_distance_noalloc", "scps_time_passes", "scps_pass_times",
            "scps_funnel_steps", "scps_funnel_mean_path", "scps_scale_by_replica", "scps_eval_zbias",
            "scps_zbias_backward", "scps_destroy",
@@ -324,8 +328,8 @@ class Context:
         """Time the launch configurations on copies of the state and keep the
         fastest; returns (path, param): path 0 persistent, 1 per-step, 2
         packed, and the persistent kernel's threads per replica or the packed
-        kernel's replicas per workgroup (an SCPS context: 1 when its
-        nonbonded pass overlaps the distance pass, else 0)."""
+        one's wavefronts per workgroup times 64 // n (an SCPS context: 1 when
+        its nonbonded pass overlaps the distance pass, else 0)."""
         px = _dev(x, torch.float32, 3 * self.sumN, "x")
         pv = _dev(v, torch.float32, 3 * self.sumN, "v")
         pc = _dev(cvstate, torch.float64, self.R * CV_STRIDE, "cvstate")
@@ -349,6 +353,13 @@ class Context:
         out = np.zeros(2, dtype=np.int32)
         _check(_lib.scps_get_launch(self._ctx(), out.ctypes.data_as(C.c_void_p)))
         return int(out[0]), int(out[1])
+
+    def get_launch_shape(self):
+        """(kernel, replicas per workgroup, workgroups per replica) of that
+        launch, kernel one of KERNELS."""
+        out = np.zeros(3, dtype=np.int32)
+        _check(_lib.scps_get_launch_shape(self._ctx(), out.ctypes.data_as(C.c_void_p)))
+        return KERNELS[out[0]], int(out[1]), int(out[2])
 
     def eval_tube(self, stack_system: int, x: torch.Tensor, s: Optional[torch.Tensor] = None,
                   w: Optional[torch.Tensor] = None):
