@@ -341,10 +341,21 @@ __device__ __forceinline__ void tile_dispatch2(const int flags, const int kb, co
 #undef SCPS_TILE2
 }
 
+// The work lists' segments are whole groups of the passes that evaluate them (one
+// tile: tile_pass with D = SCPS_PAIR_GROUP; two tiles: tile_pass2), and whole tiles
+// are whole segments (32 sub-steps of a diagonal tile, 64 of another): a group that
+// crossed the end of its segment would count its pairs twice.
+static_assert(32 % SEG_STEPS == 0 && SEG_STEPS % TAIL_STEPS == 0 && 32 % FINE_STEPS == 0, "whole segments");
+static_assert(SEG_STEPS % SCPS_PAIR_GROUP == 0 && TAIL_STEPS % SCPS_PAIR_GROUP == 0 &&
+                  FINE_STEPS % SCPS_PAIR_GROUP == 0,
+              "segments of a tile are whole groups");
+static_assert(SEG_STEPS % SCPS_PAIR_GROUP2 == 0 && TAIL_STEPS % SCPS_PAIR_GROUP2 == 0 && FINE_STEPS % 2 == 0 &&
+                  (FINE_STEPS / 2) % SCPS_PAIR_GROUP2 == 0,
+              "segments of two tiles are whole groups");
+
 // A whole tile pair, or a segment of one: sub-steps kb .. ke-1, a multiple of
-// D (every caller uses 32 or 64), evaluated SCPS_PAIR_GROUP at a time; a
-// MASK tile evaluates the per-pair predicates only on the groups whose
-// sub-step bits are set in mk.  The
+// D, evaluated SCPS_PAIR_GROUP at a time; a MASK tile evaluates the per-pair
+// predicates only on the groups whose sub-step bits are set in mk.  The
 // lane's reference values are loaded D sub-steps ahead of their use into a
 // ring of registers.
 // Outputs: fi[0..2] nonbonded, fi[3..5] contact gradient (i side); fj
@@ -356,7 +367,7 @@ __device__ __forceinline__ void tile_pass(const KParams &P, const int lane, cons
                                           const int *__restrict__ orgj, const int ncj, const float *__restrict__ rt,
                                           const float csum, float fi[6], float fj[6], float &zt) {
     constexpr int U = SCPS_PAIR_GROUP;
-    static_assert(D % U == 0, "prefetch depth is whole groups");
+    static_assert(D % U == 0 && 32 % D == 0, "prefetch depth is whole groups, whole tiles are whole depths");
     const bool low = lane < 32;
     float ring[D];
     if constexpr (CONTACT) {
