@@ -195,6 +195,11 @@ scps_status scps_set_reference_map(scps_ctx *ctx, int32_t system, int32_t n_maps
  *         0, E, 2E, ... <= n_steps, each record being a full copy of the x
  *         layout, i.e. frames is [n_steps/E + 1][3 Σ N].  record_every == 0:
  *         frames is ignored.
+ * Asynchronous.  A persistent, packed or wave launch (scps_get_launch_shape)
+ * is one kernel a call.  The split launch queues one and the per-step path a
+ * few kernels per step: the host runs at most a few thousand of them ahead of
+ * the GPU, so a call of many steps returns when the last ones are queued, and
+ * a call captured into a HIP graph is a graph of as many kernels.
  * Non-finite coordinates are flagged per replica on the device and reported
  * by scps_sync().  Requires the native map of every system (rMD) or the frame
  * stack and native map (SCPS).  Errors: INVALID_ARG, STATE, HIP. */

@@ -262,8 +262,10 @@ bool usable(scps_ctx *c, scps_status *st) {
 int pick_wg(int nb, int n_replicas) {
     const int ntile = nb * (nb + 1) / 2;
     if (ntile >= 16) return 1024;
-    // three to five blocks: a replica a CU leaves room for 16 wavefronts (17 us
-    // a step against 32 with 256 threads at 200 particles x 64)
+    // three to five blocks: a replica a CU leaves room for 16 wavefronts.  us a step
+    // with 256 or 512 threads -> 1024, any batch of 129 to 256 replicas: 130
+    // particles 20.6 -> 11.9, 192 18.7 -> 12.2, 200 20.4 -> 16.8, 256 18.5 -> 16.8,
+    // 300 29.6 -> 25.9, 320 28.5 -> 25.7
     if (ntile >= 6 && n_replicas <= 256) return 1024;
     if (ntile >= 8) return 512;
     if (ntile >= 4) return 256;
@@ -288,7 +290,9 @@ bool may_split(const scps_ctx *c, const scps_params &p) {
 // than a step inside the persistent kernel, of which the persistent kernel's own
 // idle wavefronts take back 2 on small chains: measured 7.9 us persistent
 // against 11.2 split at 120 particles x 32, 18.8 against 13.1 at 200 x 64, 47.7
-// against 40 at 560 x 128 (G = 2).
+// against 40 at 560 x 128 (G = 2).  The steps of a call do not matter: calls of one,
+// two and five steps took 0.42, 0.38 and 0.36 of the persistent kernel's time at 560
+// x 20, 0.81, 0.81 and 0.80 at 560 x 128, 0.72, 0.68 and 0.64 at 200 x 64.
 int pick_split(const scps_ctx *c) {
     double cost = 0.0;
     size_t items = 0;
@@ -380,7 +384,8 @@ void build_list(const SysHost &h, const int seg, const int seg2, const int tail_
         for (int I = 0; I <= J; ++I) {
             const int f = h.tile_flags[(size_t)I * h.nb + J];
             if (I == J) {
-                push(I, -1, J, f, 2.0 * tile_cost(f, h.tile_mask[(size_t)I * h.nb + J]));   // half the sub-steps, same cost per sub-step
+                // half the sub-steps, same cost per sub-step
+                push(I, -1, J, f, 2.0 * tile_cost(f, h.tile_mask[(size_t)I * h.nb + J]));
                 continue;
             }
             const int cls = f & (TILE_CONTACT | TILE_MASK);
@@ -1062,8 +1067,8 @@ scps_status step_impl(scps_ctx *c, float *x, float *v, double *cv, int64_t n_ste
                                         max_stack_frames(c), c->max_group, nullptr, c->d_xs, c->d_X, c->d_Q,
                                         c->xq_sets, c->kmax, -1, c->stream));
             HIP_TRY(c, launch_tube_eval(c->prm.lambda, c->kp.wscale, nullptr, c->d_jref, c->d_sysd, c->d_reps,
-                                        c->R, c->kmax, -1, c->d_X, c->d_Q, c->xq_sets, nullptr, nullptr, nullptr, 0.0, 1,
-                                        c->stream));
+                                        c->R, c->kmax, -1, c->d_X, c->d_Q, c->xq_sets, nullptr, nullptr, nullptr, 0.0,
+                                        1, c->stream));
             c->jref_init = false;
         }
         const int64_t until = record_every > 0 ? std::min(n_steps, (m / record_every + 1) * record_every) : n_steps;
@@ -1085,7 +1090,8 @@ scps_status step_impl(scps_ctx *c, float *x, float *v, double *cv, int64_t n_ste
                                         c->d_nl_cnt, c->d_nl, c->d_flags, c->stream));
             c->nl_stale = false;
             HIP_TRY(c, launch_nl_force(c->nbk, c->kp, c->d_sysd, c->d_reps, c->R, c->n_pad_max, c->d_first_chunk,
-                                       c->d_xs, c->d_nl_cnt, c->d_nl, c->d_acc, c->d_zpart_nl, c->d_rebuild, c->stream));
+                                       c->d_xs, c->d_nl_cnt, c->d_nl, c->d_acc, c->d_zpart_nl, c->d_rebuild,
+                                       c->stream));
             HIP_TRY(c, launch_integrate(c->kp, c->d_sysd, c->d_reps, c->R, c->n_pad_max, c->d_xs, c->d_vs, c->d_acc,
                                         nullptr, cv, step0 + (uint64_t)m, nullptr, c->d_flags, c->stream,
                                         c->d_first_chunk, c->d_zpart_nl, c->d_zbase, c->d_xref, c->d_rebuild));

@@ -7,7 +7,7 @@
 namespace scps {
 
 constexpr int TILE = 64;          // tile edge = wavefront width
-constexpr int KMAX = 128;         // largest SCPS frame stack (the distance pass takes it in blocks of 64)
+constexpr int KMAX = 128;         // largest SCPS frame stack (the distance pass: 8 blocks of 16, one sweep)
 constexpr int CV_STRIDE = 8;
 enum { CV_Z = 0, CV_ZM = 1, CV_EB = 2, CV_S = 3, CV_W = 4, CV_SM = 5, CV_WM = 6, CV_T = 7 };
 

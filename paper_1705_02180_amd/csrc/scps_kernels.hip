@@ -825,6 +825,9 @@ hipError_t launch_persistent_rmd(int wg, int nbk, const KParams &P, const SysDes
 // pair work at VALU issue.  us per step, persistent kernel -> split:
 //   n x replicas   560 x 2      560 x 20     560 x 64    560 x 128   971 x 12     1600 x 64    300 x 16
 //                  46.1 -> 12.2 47.2 -> 16.5 47.4 -> 25.9 47.7 -> 40 126.6 -> 23.3 440 -> 138  25.4 -> 12.2
+// A call queues n_steps + 1 launches, and the host runs at most about 2500 of them
+// ahead of the GPU: 10^4 steps of 20 x 560 hold the caller for 120 of their 158 ms (one
+// launch returned at once).
 struct SplitStep {
     const float4 *xa, *va;      // state before the update [sum n_pad], internal order
     float4 *xb, *vb;            // after it
@@ -1377,8 +1380,8 @@ __global__ __launch_bounds__(512) void k_rmd_packed(const KParams P, const SysDe
 // 12 cross-lane moves of the segment sum, then the noise).  Here a replica has a
 // wavefront to itself, C = 64 / n lanes per particle: lane c n + a takes the
 // partner steps k = c + 1, c + 1 + C, ... of particle a, WIDE_U of them side by side
-// with j-side partials of their own that move WIDE_U C lanes at a time within the copy; the copies' forces then meet in a
-// tree, z is summed over the wavefront by DPP, the noise is drawn before the
+// with j-side partials of their own that move WIDE_U C lanes at a time within the
+// copy; the copies' forces then meet in a tree, z is summed over the wavefront by DPP, the noise is drawn before the
 // pair phase (its arithmetic covers the position reads), and the first copy's
 // lanes update.  us per step of 16 replicas, packed ->
 // one wavefront per replica: n = 8 1.90 -> 1.55, 10 2.13 -> 1.53, 20 2.98 -> 1.69, 32 4.21 ->
@@ -1698,9 +1701,9 @@ __global__ __launch_bounds__(512) void k_rmd_wide(const KParams P, const SysDesc
 
 // One wavefront per replica for chains of at least 8 particles (shorter ones have
 // more copies than the tree over them gains) while it gives a SIMD (256 CUs x 4) at
-// most two.  us for 50 steps, packed / wide: n = 5 82 / 95 (1024 replicas), 10:
-// 112 / 94 (2048), 20: 160 / 112 (2048), 32: 220 / 150 (2048), 45: 1135 / 1157
-// (9000), 48: 345 / 317 (2048), 62: 905 / 911 (5000).
+// most two.  us for 50 steps, packed / wide: n = 5 82 / 95 (1024 replicas); at 2048
+// replicas 8: 102 / 93, 10: 112 / 94, 16: 139 / 89, 20: 160 / 112, 32: 219 / 150, 33:
+// 257 / 243, 48: 345 / 317, 64: 430 / 395; 45: 1135 / 1157 (9000), 62: 905 / 911 (5000).
 bool wide_default(int n_max, int n_replicas) { return n_max >= 8 && n_replicas <= 2048; }
 
 int packed_width_ok(int n_max) { return n_max >= 2 && n_max <= PACK_WMAX; }
@@ -1891,7 +1894,8 @@ __global__ __launch_bounds__(256) void k_pairs(const KParams P, const SysDesc *_
     // are any): more of them cost registers and instruction cache, and the other
     // wavefronts of the SIMD cover the loads.  us a pass with 1 / 2 / 4 groups:
     // z and gradient (64 x 3000) 263 / 272 / 317, z alone 202 / 199 / 256, forces
-    // (128 uneven chains) 349 / 336 / 362, nonbonded alone (32 x 6000) - / 618 / 552
+    // (128 uneven chains) 349 / 336 / 362, nonbonded alone (32 x 6000) - / 618 / 552,
+    // SCPS bias of the two-pass form (32 x 3000, the step) 1082 / 1085 / 1106
     constexpr int PAIR_UNROLL = MODE == PM_NB ? 4 : MODE == PM_ZG ? 1 : 2;
     tile_dispatch<MODE, NBK, PAIR_UNROLL * SCPS_PAIR_GROUP>(tf, kb, ke, it.mask, P, lane, A, shpos[wave], shorg[wave],
                                                   S.nc - J * 64, rt, cs, fi, fj, zt);
@@ -2006,8 +2010,9 @@ __device__ __forceinline__ double replica_z(const int *__restrict__ first, const
 // one of its particles has moved more than NL_SKIN / 2 since the last build
 // (whatever moved it: steps, or the caller between calls), so no pair within
 // the cutoffs is ever missing.  The host forces a rebuild of every replica
-// when the lists are new or the reference map they carry has changed.  The build tests only the tile pairs whose blocks' bounding
-// spheres come within r_list.  Entry: x = j | contact << 30 | nonbonded << 29
+// when the lists are new or the reference map they carry has changed.  The
+// build tests only the tile pairs whose blocks' bounding spheres come within
+// r_list.  Entry: x = j | contact << 30 | nonbonded << 29
 // (j internal, predicates of the pair), y = the bits of R_ij (float32).
 // Skipped contact pairs have C = 0, so
 //   z = sum over all counted pairs of R^2 + sum over listed pairs of C (C - 2R)

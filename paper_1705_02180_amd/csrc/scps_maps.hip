@@ -1217,12 +1217,16 @@ __device__ __forceinline__ void scps_bias_consume(const KParams &P, const SysDes
 }
 
 // BIG: stacks of 65 .. KMAX frames, HALF: no group of more than 16 replicas, in
-// kernels of their own so that each keeps its register allocation.  A sub-step's matrix work is
-// cut to the smallest of a few frame counts that holds the stack and to 16 or
-// 32 replicas, and a pair wavefront's to its replicas: 20 replicas x 1501
-// particles, 72 frames took 230 us a pass as 32 replicas with 128 frames,
-// 168 now; 8 x 2500 (1252 in contact), 33 frames 71 us as 32,
-// 33 now; 15 x 1700, 70 frames 241 -> 122 us.
+// kernels of their own so that each keeps its register allocation.  A sub-step's
+// matrix work is cut to the smallest of a few frame counts that holds the stack and
+// to 16 or 32 replicas, and a pair wavefront's to its replicas.  The counts are steps
+// of 8 to 32 frames, with one at 52 and one at 72, where the paths of the protocol
+// lie (10^4 steps with a frame every 200; about 72 frames to a path): each more is
+// another form of the producer to compile and to hold in the instruction cache.  us
+// a pass as 32 replicas x 64 or 128 frames -> so cut -> with the workgroups per tile
+// of launch_scps_bias: 20 replicas x 1501 particles, 72 frames 230 -> 168 -> 142; 8 x
+// 2500 (1252 in contact), 33 frames 71 -> 33; 15 x 1700, 70 frames 241 -> 122 -> 108.
+// A step of 32 x 1500 particles: 72 frames 311 us, 73 320, 96 344, 97 399, 128 402.
 template <bool BIG, bool HALF>
 __device__ __forceinline__ void scps_bias_produce_any(const SysDesc &S, const ScpsItem &it, const int lane,
                                                       const int wave, const int kb, const int ke, BiasLds &L) {
@@ -1392,12 +1396,10 @@ hipError_t launch_scps_dist(const KParams &P, const SysDesc *sysd, const RepDesc
     if (n_items == 0) return hipSuccess;
     if (sets != 1 && sets != XQ_SETS) return hipErrorInvalidValue;
     if (max_frames < 1 || max_frames > KMAX || max_frames > kmax) return hipErrorInvalidValue;
-#define SCPS_DIST(NB)                                                                                              \
-    do {                                                                                                           \
-        if (max_group <= 16)                                                                                       \
-            launch_scps_dist_as<1, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, sets, kmax, stack_sys, st); \
-        else                                                                                                       \
-            launch_scps_dist_as<2, NB>(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, sets, kmax, stack_sys, st); \
+#define SCPS_DIST(NB)                                                                                           \
+    do {                                                                                                        \
+        const auto launch = max_group <= 16 ? launch_scps_dist_as<1, NB> : launch_scps_dist_as<2, NB>;          \
+        launch(P, sysd, reps, groups, items, n_items, jref, xs, X, Q, sets, kmax, stack_sys, st);               \
     } while (0)
     switch ((max_frames + 15) / 16) {
     case 1: SCPS_DIST(1); break;
@@ -1480,9 +1482,9 @@ hipError_t launch_scps_bias(const KParams &P, const SysDesc *sysd, const RepDesc
         }
     }
     const int grid = std::min(n_items * ks, 256);
-#define SCPS_LAUNCH(BIG, HALF)                                                                                     \
-    hipLaunchKernelGGL((k_scps_bias<BIG, HALF>), dim3(grid), dim3(BIAS_WG), 0, st, P, sysd, reps, groups, items, n_items, \
-                       xs, coef, csum, kmax, ks, acc)
+#define SCPS_LAUNCH(BIG, HALF)                                                                                  \
+    hipLaunchKernelGGL((k_scps_bias<BIG, HALF>), dim3(grid), dim3(BIAS_WG), 0, st, P, sysd, reps, groups, items, \
+                       n_items, xs, coef, csum, kmax, ks, acc)
     if (max_frames > 64) {
         if (max_group <= 16)
             SCPS_LAUNCH(true, true);
